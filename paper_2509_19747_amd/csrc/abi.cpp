@@ -218,22 +218,39 @@ KernelOp kernel_op_of(const rr_precond& P) {
     k.scale = P.op.scale;
     k.xd = P.xd.as<double>();
     k.hd = P.hd.as<double>();
+    k.rrec = P.rrec.ptr();
+    k.crec = P.crec.ptr();
+    k.xp = P.xp.as<double>();
     return k;
 }
 
-void setup_operator(rr_precond& P, hipStream_t st) {
+void setup_operator(rr_precond& P, hipStream_t st, int products) {
     const rr_operator& A = P.op;
     const int64_t n = A.n;
     if (is_kernel(A)) {
         const int dm = kernel_record_len(A.d);
-        P.sqn.reset(&P.alloc, (size_t)n * sizeof(float));
-        launch_sqnorms(A.pts, n, A.d, P.sqn.as<float>(), st);
-        P.xa.reset(&P.alloc, (size_t)n * dm * sizeof(float));
-        launch_point_records(A.pts, n, A.d, dm, P.xa.as<float>(), st);
-        P.xd.reset(&P.alloc, (size_t)n * dm * sizeof(double));
-        P.hd.reset(&P.alloc, (size_t)n * sizeof(double));
-        launch_point_records64(A.pts, n, A.d, dm, kernel_g64(A.kind, A.kconst), P.xd.as<double>(),
-                               P.hd.as<double>(), st);
+        const bool mma = kernel_mma_ok(n, A.d);
+        // an operator that only multiplies needs its MFMA products' records alone
+        if (products == SETUP_ALL || !mma) {
+            P.sqn.reset(&P.alloc, (size_t)n * sizeof(float));
+            launch_sqnorms(A.pts, n, A.d, P.sqn.as<float>(), st);
+            P.xa.reset(&P.alloc, (size_t)n * dm * sizeof(float));
+            launch_point_records(A.pts, n, A.d, dm, P.xa.as<float>(), st);
+            P.xd.reset(&P.alloc, (size_t)n * dm * sizeof(double));
+            P.hd.reset(&P.alloc, (size_t)n * sizeof(double));
+            launch_point_records64(A.pts, n, A.d, dm, kernel_g64(A.kind, A.kconst), P.xd.as<double>(),
+                                   P.hd.as<double>(), st);
+        }
+        if (mma && products != SETUP_WORK) {
+            P.xp.reset(&P.alloc, kernel_mma_record64_bytes(n, dm));
+            if (!P.hd.ptr()) P.hd.reset(&P.alloc, (size_t)n * sizeof(double));
+            launch_kmma_records64(kernel_op_of(P), P.xp.as<double>(), P.hd.as<double>(), st);
+        }
+        if (mma && P.opts.prec != RR_PREC_FP64 && products != SETUP_F64) {
+            P.rrec.reset(&P.alloc, kernel_mma_record_bytes(n, dm));
+            P.crec.reset(&P.alloc, kernel_mma_record_bytes(n, dm));
+            launch_kmma_records(kernel_op_of(P), P.rrec.ptr(), P.crec.ptr(), st);
+        }
     } else if (P.opts.prec != RR_PREC_FP64) {
         P.A32.reset(&P.alloc, (size_t)n * n * sizeof(float));
         launch_copy_mat(DT_F64, A.A, A.lda, DT_F32, P.A32.ptr(), n, n, n, st);
@@ -536,7 +553,7 @@ rr_status rr_apply_operator_block(const rr_operator* A, double mu, int32_t prec,
         const size_t ws = is_kernel(*A) ? kernel_matvec_ws_doubles(A->n, A->d, nr) : 0;
         DBuf part(&P.alloc, ((size_t)operator_part_count(P) * nr + 1) * sizeof(double));
         DBuf kws(&P.alloc, (ws + 1) * sizeof(double));
-        setup_operator(P, st);
+        setup_operator(P, st, prec == RR_PREC_FP64 ? SETUP_F64 : SETUP_WORK);
         apply_operator_multi(P, U, nr, mu, Y, part.as<double>(), kws.as<double>(),
                              prec == RR_PREC_FP64, st);
         RR_HIP(hipGetLastError());
@@ -569,7 +586,7 @@ rr_status rr_operator_delta_norm(const rr_operator* A, int32_t prec, int32_t ite
         DBuf kws(&P.alloc, (ws + 1) * sizeof(double));
         DBuf v(&P.alloc, n * sizeof(double)), y1(&P.alloc, n * sizeof(double)), y2(&P.alloc, n * sizeof(double));
         DBuf vp(&P.alloc, ((size_t)vec_blocks(n) + 1) * sizeof(double)), sc(&P.alloc, 4 * sizeof(double));
-        setup_operator(P, st);
+        setup_operator(P, st, SETUP_PRODUCTS);
         launch_gauss_fill(v.ptr(), DT_F64, n, 1, n, seed, st);
         launch_dot_part(n, v.as<double>(), v.as<double>(), vp.as<double>(), st);
         launch_normalize(n, v.as<double>(), v.as<double>(), vp.as<double>(), vec_blocks(n), sc.as<double>() + 1, st);

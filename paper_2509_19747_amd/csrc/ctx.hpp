@@ -176,6 +176,8 @@ struct rr_precond {
     rr::DBuf A32;         // float32 copy of a dense A (FP32 / MIXED)
     rr::DBuf sqn;         // |x_i|^2 (kernel operators)
     rr::DBuf xa;          // padded point records (kernel operators)
+    rr::DBuf rrec, crec;  // packed bf16 records of the MFMA matvec (float32-class handles)
+    rr::DBuf xp;          // packed float64 records of the float64 MFMA matvec
     rr::DBuf xd, hd;      // float64 point records and -g |x_i|^2 / 2 (kernel operators)
     // basis
     rr::DBuf Omega;       // n x l, dtype omega_dt
@@ -217,8 +219,11 @@ void apply_operator_multi(const rr_precond& P, const double* U, int nr, double m
                           bool estimate = false);
 int operator_part_count(const rr_precond& P);
 // Operator setup (A0): squared norms and point records for kernels, the float32
-// copy of a dense A when the working precision is below float64.
-void setup_operator(rr_precond& P, hipStream_t st);
+// copy of a dense A when the working precision is below float64.  products: the whole
+// handle, or only what the operator products read (both precisions, the working one,
+// the float64 one).
+enum { SETUP_ALL = 0, SETUP_PRODUCTS, SETUP_WORK, SETUP_F64 };
+void setup_operator(rr_precond& P, hipStream_t st, int products = SETUP_ALL);
 size_t operator_ws_doubles(const rr_precond& P);
 
 // z = rcoef*r + Qb (Kc (Qb^T r)), with partials of r^T z.  Returns #partials.

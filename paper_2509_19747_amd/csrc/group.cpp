@@ -159,14 +159,14 @@ struct GroupEngine::Impl {
             for (Job* j : jobs) {
                 Batch& b = *j->bt;
                 const KernelOp k = kernel_op_of(b.P);
-                const KmmaPlanInfo pl = kernel_mma_plan_info(b.n);
                 const int nfb = kernel_matvec_blocks(b.n);
                 for (int64_t c0 = 0; c0 < b.m;) {
                     const int nr = Batch::mat_width(b.m, c0, k.dm);
                     if (L == group_mat_list(k.kind, k.dm, nr)) {
+                        const KmmaPlanInfo pl = kernel_mma_plan_info(b.n, k.kind, nr);
                         GPair& g = pairs[np++];
-                        g.xa = k.xa;
-                        g.sqn = k.sqn;
+                        g.rrec = (const bf16x8_t*)k.rrec;
+                        g.crec = (const bf16x8_t*)k.crec;
                         g.u = b.Pm.as<double>() + c0 * b.n;
                         g.part = b.gpart.as<double>() + (size_t)c0 * b.gpart_doubles;
                         g.y = b.W.as<double>() + c0 * b.n;
@@ -181,10 +181,12 @@ struct GroupEngine::Impl {
                         g.nb = pl.nb;
                         g.m = pl.m;
                         g.S = pl.S;
+                        g.units = pl.units;
+                        g.items = pl.items;
                         g.nfb = nfb;
                         g.w_mat = w;
                         g.w_fin = wf;
-                        w += (int)pl.items;
+                        w += pl.items;
                         wf += nfb;
                     }
                     c0 += nr;

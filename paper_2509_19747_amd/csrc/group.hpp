@@ -24,6 +24,7 @@
 #include "../../include/randrand.h"
 #include "common.hpp"
 #include "kernels.hpp"
+#include "kmma.hpp"
 
 namespace rr {
 
@@ -46,8 +47,8 @@ struct GList {
 // One block of nr consecutive columns of one request (nr = 1, 2 or 4; the last
 // nr - ncols are zero padding): the kernel product and its finish.
 struct GPair {
-    const float* xa;
-    const float* sqn;
+    const bf16x8_t* rrec;   // packed row and column records
+    const bf16x8_t* crec;
     const double* u;        // nr columns, leading dimension n
     double* part;           // slot partials of the block
     double* y;              // nr columns
@@ -57,10 +58,9 @@ struct GPair {
     double scale, mu;
     float c;
     int32_t nr, ncols;
-    int32_t nb, m, S;       // work-item plan of the product
+    int32_t nb, m, S, units, items;   // work-item plan of the product
     int32_t nfb;            // finish blocks
     int32_t w_mat, w_fin;   // first work item within the GL_MAT and GL_FIN lists
-    int32_t pad;
 };
 
 // One request: the fused x, r and p updates of its m columns.

@@ -194,7 +194,17 @@ struct KernelOp {
     double kconst, scale;
     const double* xd = nullptr;   // float64 point records: n x dm doubles (coordinates, zeros)
     const double* hd = nullptr;   // -g |x_i|^2 / 2 in float64 (g of kernel_g64)
+    const void* rrec = nullptr;   // packed row and column records of the MFMA matvec
+    const void* crec = nullptr;
+    const double* xp = nullptr;   // packed float64 records of the float64 MFMA matvec
 };
+// Packed bf16 records (kmma.hpp) of launch_kernel_matvec_mma: kernel_mma_record_bytes
+// for each of the two arrays, filled from op.pts (kind, n, d, dm and kconst of op).
+size_t kernel_mma_record_bytes(int64_t n, int dm);
+void launch_kmma_records(const KernelOp& op, void* rrec, void* crec, hipStream_t st);
+// The same for launch_kernel_matvec_mma64 (op.xp).
+size_t kernel_mma_record64_bytes(int64_t n, int dm);
+void launch_kmma_records64(const KernelOp& op, double* xp, double* hd, hipStream_t st);
 // float64 exponent scale g: an RBF entry is exp2(-g r^2 / 2) with g = 2 kconst log2(e);
 // a Matern-3/2 entry uses g = 1 (the record product is then -r^2 / 2).
 double kernel_g64(int kind, double kconst);
@@ -217,9 +227,6 @@ void launch_point_records(const float* pts, int64_t n, int d, int dm, float* xa,
 int kernel_matvec_blocks(int64_t n);
 // Workspace (doubles) of launch_kernel_matvec(_multi) for up to nr columns.
 size_t kernel_matvec_ws_doubles(int64_t n, int d, int nr);
-// The same for one precision only (fp64: the float64 operator on point records;
-// otherwise the float32-class operator): what launch_kernel_matvec_multi uses then.
-size_t kernel_matvec_ws_doubles_for(int64_t n, int d, int nr, bool fp64);
 void launch_kernel_matvec(const KernelOp& op, bool fp64, const double* u, double mu, double* y,
                           double* dot_part, double* ws, const int32_t* stop, hipStream_t st);
 // nr >= 1 right-hand sides at once: u, y are n x nr (leading dimension n);
@@ -235,14 +242,14 @@ void launch_kernel_matvec_multi(const KernelOp& op, bool fp64, const double* u, 
 bool kernel_mma_ok(int64_t n, int d);
 size_t kernel_mma_ws_doubles(int64_t n, int nr);
 // Work-item plan of the MFMA kernel product (row blocks nb, column blocks per run m,
-// column ranges S, items per column block of the launch).
+// column ranges S, units, items a column block of nr columns is launched in).
 struct KmmaPlanInfo {
-    int nb, m, S;
-    int64_t items;
+    int nb, m, S, units, items;
 };
-KmmaPlanInfo kernel_mma_plan_info(int64_t n);
+KmmaPlanInfo kernel_mma_plan_info(int64_t n, int kind, int nr);
 // Columns one MFMA kernel product may carry with float64 sums (4 for records of up to
-// 16 terms, else 2); each column's arithmetic is the same whatever the width.
+// 16 terms, else 2; pairs of columns share a block); each column's arithmetic is the
+// same whatever the width.
 int kernel_mma_max_cols(int dm);
 // a32: float32 products and partial sums (estimate grade, power iterations).
 void launch_kernel_matvec_mma(const KernelOp& op, const double* u, int nr, double mu, double* y,

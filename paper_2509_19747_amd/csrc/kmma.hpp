@@ -43,6 +43,23 @@ struct KmmaShape {
 constexpr int kmma_apiece(int seg) { return seg == 2 || seg == 4 ? 1 : seg == 5 ? 2 : 0; }
 constexpr int kmma_bpiece(int seg) { return seg == 1 || seg == 4 ? 1 : seg == 3 ? 2 : 0; }
 
+// Packed records.  For DM >= 16 a step's chunk is one piece of 16 coordinates, and the
+// same piece serves several steps (piece 0 three of the six segments): a record holds
+// only UC distinct chunks, chunk kmma_uc(s) being the operand of step s.  Shorter
+// records mix segments within a step and keep every step's chunk.
+// Layout of the packed arrays: 32-point tiles of UC units of 64 x 16 bytes; lane
+// l = 32 h + p of unit c holds the 8 terms that half h supplies for point p of the
+// tile, so a unit is one contiguous 1 KB operand of a wave, in memory and in LDS.
+template <int DM>
+constexpr int kmma_chunks() { return DM >= 16 ? 3 * (DM / 16) + 1 : KmmaShape<DM>::KB; }
+template <int DM, bool ROW>
+constexpr int kmma_uc(int s) {
+    if (DM < 16) return s;
+    if (16 * s >= 6 * DM) return 3 * (DM / 16);
+    const int seg = 16 * s / DM;
+    return (ROW ? kmma_apiece(seg) : kmma_bpiece(seg)) * (DM / 16) + 16 * s % DM / 16;
+}
+
 // Exact split v = p[0] + p[1] + p[2] into bf16 pieces (normal-range v).
 RR_DEV void kmma_split3(float v, __bf16 (&p)[3]) {
     p[0] = (__bf16)v;

@@ -19,10 +19,13 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = (size_t)64 << 20;   // 64 MiB per device
+// What a call may count against (accepted_bytes), and the array, which also holds what
+// the packed records take beyond that count (at most 10 MiB for any accepted operator).
+constexpr size_t kScratchBytes = (size_t)64 << 20;
+constexpr size_t kArrayBytes = (size_t)80 << 20;
 constexpr int kMaxDevices = 64;
 
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+__device__ __align__(256) unsigned char scratch[kArrayBytes];
 
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
@@ -56,7 +59,7 @@ struct Carve {
 };
 
 struct Layout {
-    size_t sqn = 0, xa = 0, xd = 0, hd = 0, a32 = 0, part = 0, ws = 0, total = 0;
+    size_t rrec = 0, crec = 0, xp = 0, hd = 0, a32 = 0, part = 0, ws = 0, total = 0;
 };
 
 Layout layout_for(const rr_operator& A, int32_t prec) {
@@ -65,18 +68,41 @@ Layout layout_for(const rr_operator& A, int32_t prec) {
     const int64_t n = A.n;
     if (rr::is_kernel(A)) {
         const int dm = rr::kernel_record_len(A.d);
-        L.sqn = c.take((size_t)n * sizeof(float));
-        L.xa = c.take((size_t)n * dm * sizeof(float));
-        L.xd = c.take((size_t)n * dm * sizeof(double));
-        L.hd = c.take((size_t)n * sizeof(double));
+        if (prec == RR_PREC_FP64) {
+            L.xp = c.take(rr::kernel_mma_record64_bytes(n, dm));
+            L.hd = c.take((size_t)n * sizeof(double));
+        } else {
+            L.rrec = c.take(rr::kernel_mma_record_bytes(n, dm));
+            L.crec = c.take(rr::kernel_mma_record_bytes(n, dm));
+        }
         L.part = c.take((size_t)rr::kernel_matvec_blocks(n) * sizeof(double));
-        L.ws = c.take((rr::kernel_matvec_ws_doubles_for(n, A.d, 1, prec == RR_PREC_FP64) + 1) * sizeof(double));
+        L.ws = c.take((rr::kernel_mma_ws_doubles(n, 1) + 1) * sizeof(double));
     } else {
         if (prec != RR_PREC_FP64) L.a32 = c.take((size_t)n * n * sizeof(float));
         L.part = c.take((size_t)rr::dense_matvec_blocks(n) * sizeof(double));
     }
     L.total = c.off;
     return L;
+}
+
+// The bytes that a call counts against kScratchBytes: float32 and float64 point records,
+// norms and the slot partials for a kernel operator, the float32 copy for a dense one.
+size_t accepted_bytes(const rr_operator& A, int32_t prec) {
+    Carve c;
+    const int64_t n = A.n;
+    if (rr::is_kernel(A)) {
+        const int dm = rr::kernel_record_len(A.d);
+        c.take((size_t)n * sizeof(float));
+        c.take((size_t)n * dm * sizeof(float));
+        c.take((size_t)n * dm * sizeof(double));
+        c.take((size_t)n * sizeof(double));
+        c.take((size_t)rr::kernel_matvec_blocks(n) * sizeof(double));
+        c.take((rr::kernel_mma_ws_doubles(n, 1) + 1) * sizeof(double));
+    } else {
+        if (prec != RR_PREC_FP64) c.take((size_t)n * n * sizeof(float));
+        c.take((size_t)rr::dense_matvec_blocks(n) * sizeof(double));
+    }
+    return c.off;
 }
 
 }  // namespace
@@ -90,10 +116,11 @@ extern "C" rr_status rr_apply_operator_noalloc(const rr_operator* A, double mu, 
         RR_REQUIRE(u != nullptr && y != nullptr, "u or y is null");
         RR_REQUIRE(std::isfinite(mu), "mu must be finite");
         RR_REQUIRE(prec >= 0 && prec <= 2, "unknown precision");
+        const size_t need = accepted_bytes(*A, prec);
         const Layout L = layout_for(*A, prec);
-        if (L.total > kScratchBytes)
+        if (need > kScratchBytes || L.total > kArrayBytes || (is_kernel(*A) && !kernel_mma_ok(A->n, A->d)))
             throw RrError{RR_EINVAL, "operator too large for the no-allocation scratch: needs " +
-                                         std::to_string(L.total) + " bytes, the scratch holds " +
+                                         std::to_string(need) + " bytes, the scratch holds " +
                                          std::to_string(kScratchBytes)};
         require_device();
         unsigned char* base = (unsigned char*)scratch_on_device();
@@ -109,14 +136,17 @@ extern "C" rr_status rr_apply_operator_noalloc(const rr_operator* A, double mu, 
             k.dm = kernel_record_len(A->d);
             k.kconst = A->kconst;
             k.scale = A->scale;
-            k.sqn = (const float*)(base + L.sqn);
-            k.xa = (const float*)(base + L.xa);
-            k.xd = (const double*)(base + L.xd);
-            k.hd = (const double*)(base + L.hd);
-            launch_sqnorms(A->pts, n, A->d, (float*)(base + L.sqn), st);
-            launch_point_records(A->pts, n, A->d, k.dm, (float*)(base + L.xa), st);
-            launch_point_records64(A->pts, n, A->d, k.dm, kernel_g64(A->kind, A->kconst), (double*)(base + L.xd),
-                                   (double*)(base + L.hd), st);
+            k.sqn = nullptr;
+            k.xa = nullptr;
+            if (prec == RR_PREC_FP64) {
+                k.xp = (const double*)(base + L.xp);
+                k.hd = (const double*)(base + L.hd);
+                launch_kmma_records64(k, (double*)(base + L.xp), (double*)(base + L.hd), st);
+            } else {
+                k.rrec = base + L.rrec;
+                k.crec = base + L.crec;
+                launch_kmma_records(k, base + L.rrec, base + L.crec, st);
+            }
             launch_kernel_matvec(k, prec == RR_PREC_FP64, u, mu, y, part, (double*)(base + L.ws), nullptr, st);
         } else if (prec != RR_PREC_FP64) {
             float* a32 = (float*)(base + L.a32);

@@ -78,6 +78,30 @@ def test_kernel_matvec(kind, n, d):
 
 
 @pytest.mark.parametrize("kind", [rr.OP_RBF, rr.OP_MATERN32])
+@pytest.mark.parametrize("n,d", [(5633, 8), (7937, 16), (11_777, 3), (20_001, 20), (32_700, 16)])
+def test_kernel_matvec_plan_edges(kind, n, d):
+    """Sizes on both sides of the work-item plan's changes (four, two and one column ranges
+    a block, runs of one and two column blocks; ragged last block): sampled rows against
+    the oracle's kernel formula, both precisions, and a three-column block equal to its
+    columns bitwise."""
+    from oracle.operators import kernel_block
+    rng = np.random.default_rng(n)
+    pts = rng.standard_normal((d, n)).astype(np.float32)
+    kconst, scale, mu = 0.5 / d, 1.0 / n, 1e-3
+    U = rng.standard_normal((n, 3))
+    rows = np.unique(np.r_[0, 255, 256, n - 1, n // 256 * 256, rng.integers(0, n, 60)])
+    K = kernel_block(kind, kconst, pts.T[rows].astype(np.float64), pts.T.astype(np.float64))
+    ref = scale * (K @ U) + mu * U[rows]
+    kop = rr.kernel_operator(kind, _cuda(pts), kconst, scale)
+    for prec, tol in (("fp32", 2e-6), ("fp64", 1e-12)):
+        Y = rr.apply_operator_block(kop, mu, prec, _cuda(U)).cpu().numpy()
+        assert np.linalg.norm(Y[rows] - ref) <= tol * np.linalg.norm(ref), prec
+        for q in range(3):
+            y = rr.apply_operator(kop, mu, prec, _cuda(U[:, q])).cpu().numpy()
+            assert np.array_equal(y, Y[:, q]), (prec, q)
+
+
+@pytest.mark.parametrize("kind", [rr.OP_RBF, rr.OP_MATERN32])
 @pytest.mark.parametrize("n,d,nr", [(5000, 16, 1), (5000, 16, 2), (4100, 5, 3), (3001, 20, 5),
                                     (4500, 8, 8), (2600, 4, 13)])
 def test_kernel_matvec_block_multi_tile(kind, n, d, nr):
