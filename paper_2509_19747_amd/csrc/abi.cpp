@@ -246,7 +246,7 @@ void setup_operator(rr_precond& P, hipStream_t st, int products) {
             if (!P.hd.ptr()) P.hd.reset(&P.alloc, (size_t)n * sizeof(double));
             launch_kmma_records64(kernel_op_of(P), P.xp.as<double>(), P.hd.as<double>(), st);
         }
-        if (mma && P.opts.prec != RR_PREC_FP64 && products != SETUP_F64) {
+        if (P.opts.prec != RR_PREC_FP64 && products != SETUP_F64) {
             P.rrec.reset(&P.alloc, kernel_mma_record_bytes(n, dm));
             P.crec.reset(&P.alloc, kernel_mma_record_bytes(n, dm));
             launch_kmma_records(kernel_op_of(P), P.rrec.ptr(), P.crec.ptr(), st);

@@ -33,7 +33,7 @@ struct Batch {
     const Alloc* al;
     DBuf R, Pm, Z, W, T, parts, C, Dall, D, state, start, target2, mucol, muidx, gws;
     DBuf cidx, mucomp;    // column list and shifts of a compact restart product
-    DBuf kws, kdot;       // symmetric multi-column kernel matvec (few columns)
+    DBuf kws, kdot;       // symmetric multi-column kernel matvec (few columns); kws: also the wide product
     bool kmulti = false;
     DBuf cpart, dcols, rzp;   // projection through the basis, groups of up to 8 columns
     int pmax = 0, gch = 1;
@@ -99,6 +99,8 @@ struct Batch {
         if (kmulti) {
             kws.reset(al, (kernel_matvec_ws_doubles(n, p.op.d, (int)std::min<int64_t>(m, 8)) + 1) * sizeof(double));
             kdot.reset(al, (size_t)kernel_matvec_blocks(n) * mp * sizeof(double));
+        } else if (is_kernel(p.op) && p.opts.prec != RR_PREC_FP64) {
+            kws.reset(al, kernel_matmat_ws_bytes(n, m));
         }
         rrp.reset(al, (size_t)bxr_blocks(n) * m * sizeof(double));
         cnt.reset(al, (size_t)2 * m * sizeof(int32_t));
@@ -177,7 +179,8 @@ struct Batch {
         }
         if (is_kernel(P.op)) {
             const KernelOp k = kernel_op_of(P);
-            launch_kernel_matmat_f64(k, fp64 || P.opts.prec == RR_PREC_FP64, muc, Pin, ldp, mc, Wout, n, st);
+            if (fp64 || P.opts.prec == RR_PREC_FP64) launch_kernel_matmat_f64(k, muc, Pin, ldp, mc, Wout, n, st);
+            else launch_kernel_matmat_bf16x6(k, muc, Pin, ldp, mc, Wout, n, kws.ptr(), kws.bytes(), st);
         } else {
             if (!fp64 && P.A32.ptr()) gemm(false, false, n, mc, n, P.A32.ptr(), n, Pin, ldp, Wout, n, 1.0, 0.0, DT_F32);
             else gemm(false, false, n, mc, n, P.op.A, P.op.lda, Pin, ldp, Wout, n, 1.0, 0.0);

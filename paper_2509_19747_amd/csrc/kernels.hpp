@@ -284,11 +284,16 @@ void launch_dense_gemm_bf16(int64_t n, int64_t m, const void* A, int64_t lda, co
                             int64_t ldb, double mu, float* Y, int64_t ldy, hipStream_t st);
 
 // ------------------------------------------------------------ batched solve
-// W = scale*K P + diag(mucol) P for m columns on float64 MFMA; entries in float32
-// (the same values as the single-vector matvec) or, with f64_entries, float64.
-void launch_kernel_matmat_f64(const KernelOp& op, bool f64_entries, const double* mucol,
-                              const double* P, int64_t ldp, int64_t m, double* W, int64_t ldw,
-                              hipStream_t st);
+// W = scale*K P + diag(mucol) P for m columns on float64 MFMA with float64 entries.
+void launch_kernel_matmat_f64(const KernelOp& op, const double* mucol, const double* P, int64_t ldp, int64_t m,
+                              double* W, int64_t ldw, hipStream_t st);
+// The same in the working precision (kernels_kgemm.hip): float32-class entries times P in
+// float32 by exact bf16 pieces; needs op.rrec and op.crec; ws: kernel_matmat_ws_bytes for n
+// and at least m columns.
+size_t kernel_matmat_ws_bytes(int64_t n, int64_t m);
+void launch_kernel_matmat_bf16x6(const KernelOp& op, const double* mucol, const double* P, int64_t ldp, int64_t m,
+                                 double* W, int64_t ldw, void* ws, size_t ws_bytes,
+                                 hipStream_t st);
 void launch_add_shift_cols(int64_t n, int64_t m, const double* mucol, const double* P, int64_t ldp,
                            double* W, int64_t ldw, hipStream_t st);
 int coldot_chunks(int64_t n);

@@ -147,6 +147,37 @@ RR_DEV void kmma_record(const float* __restrict__ rec, float sq, float g, int h,
     kmma_record_x<DM, ROW>(xr, sq, g, h, emit);
 }
 
+// Copies 16 bytes per lane from src + 16 lane (4 bytes: the second form from src + voff,
+// voff in bytes, the third from each lane's own address) to the LDS bytes from
+// off + 16 lane (off + 4 lane) on, without passing through registers; src and off are
+// wave-uniform.  The copy has no register output, so nothing can be overwritten in
+// flight, and it is complete after the wave's own vmcnt wait.  The compiler does not
+// track it (its tracking of the builtin would hold every LDS read of the buffer's other
+// half back until the copy is done); M0 has no other user in these kernels.
+template <typename P>
+RR_DEV const P* uniform_ptr(const P* p) {
+    const uint64_t v = reinterpret_cast<uintptr_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return reinterpret_cast<const P*>(((uint64_t)hi << 32) | lo);
+}
+RR_DEV void lds_copy16(const void* src, int lane, uint32_t off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(__builtin_amdgcn_readfirstlane(off)), "v"(16 * lane), "s"(uniform_ptr((const char*)src))
+                 : "memory");
+}
+RR_DEV void lds_copy4(const void* src, int voff, uint32_t off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+                 :
+                 : "s"(__builtin_amdgcn_readfirstlane(off)), "v"(voff), "s"(uniform_ptr((const char*)src))
+                 : "memory");
+}
+RR_DEV void lds_copy4_lanes(const void* src, uint32_t off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
+                 :
+                 : "s"(__builtin_amdgcn_readfirstlane(off)), "v"(src)
+                 : "memory");
+}
 // Entry from the record product t (see above).
 template <int KIND>
 RR_DEV float kmma_entry(float t, float c) {

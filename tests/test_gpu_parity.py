@@ -667,6 +667,36 @@ def test_kernel_fp32_bf16_sketch_basis(n, l, sketch):
     assert abs(info["iters"] - ref.iters) <= max(3, int(0.1 * ref.iters))
 
 
+@pytest.mark.parametrize("kind,n,d,m", [(rr.OP_RBF, 130, 3, 33), (rr.OP_RBF, 777, 8, 64), (rr.OP_MATERN32, 1025, 16, 65),
+                                        (rr.OP_RBF, 2081, 20, 129), (rr.OP_MATERN32, 600, 4, 200),
+                                        (rr.OP_RBF, 1500, 16, 1030)])
+def test_wide_kernel_product(kind, n, d, m):
+    """The working-precision product of more than 32 columns: with the refinement off, a
+    batched solve's final residuals come from it, and differ from the exact ones of the same
+    X by at most the float32 class's 2^-21 of |A| |x| per row.  Row and column remainders,
+    both column-block widths, several column chunks, and columns whose sizes lie outside
+    float32's range."""
+    rng = np.random.default_rng(n + m)
+    pts = rng.standard_normal((d, n)).astype(np.float32)
+    kconst, mu = 0.5 / d, 1e-2
+    op = Operator(kind=kind, pts=pts, kconst=kconst, scale=1.0 / n)
+    B = rng.standard_normal((n, m))
+    B[:, 0] *= 1e-60
+    B[:, 1] *= 1e-35
+    B[:, m - 1] *= 1e50
+    kop = rr.kernel_operator(kind, _cuda(pts), kconst, 1.0 / n)
+    P = rr.build_precond(kop, [mu], l=20, sketch="gaussian", seed=5, prec="fp32")
+    X, infos, st = P.solve_batch(_cuda(B), [0] * m, tol=1e-4, fp64_ir=0, certify=False)
+    X = X.cpu().numpy()
+    assert st == rr.RR_OK
+    R = B - (op.matmat(X) + mu * X)
+    E = 2.0**-21 * (op.matmat(np.abs(X)) + mu * np.abs(X))
+    for j in range(m):
+        nb = np.linalg.norm(B[:, j])
+        assert abs(infos[j]["relres_work"] - np.linalg.norm(R[:, j]) / nb) <= np.linalg.norm(E[:, j]) / nb, j
+        assert infos[j]["relres_work"] <= 1e-4
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 def test_batched_multi_shift_matches_single_and_oracle(prec):
     # every RHS under every shift (joint basis), one fused batched solve, compared with
