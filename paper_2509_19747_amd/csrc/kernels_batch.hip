@@ -15,12 +15,14 @@
 namespace rr {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-constexpr int KD_BM = 256, KD_BN = 128, KD_BK = 16, KD_THREADS = 1024;
+constexpr int KD_BM = 128, KD_BN = 128, KD_BK = 16, KD_THREADS = 512;
 
-// Block: 16 waves in a 4 (rows) x 4 (columns) grid of 64 x 32 wave tiles (4 x 2
-// MFMA tiles, 32 float64 accumulators per lane), four waves per SIMD: the float64
-// MFMA pipe needs several resident waves to stay busy.  Per step of 16 points the
-// block forms the 256 x 16 kernel tile (thread: one row, 4 points whose records
+// Block: 8 waves in a 2 (rows) x 4 (columns) grid of 64 x 32 wave tiles (4 x 2 MFMA
+// tiles, 32 float64 accumulators per lane), two blocks per compute unit: the float64
+// MFMA pipe needs several resident waves to stay busy, and one block forms entries while
+// the other multiplies (n = 20,000, 256 columns: 6.6 ms; one block of 256 rows a compute
+// unit left 98 units idle and took 17.2).  Per step of 16 points the
+// block forms the 128 x 16 kernel tile (thread: one row, 4 points whose records
 // arrive through scalar loads; float64 entries: difference form, float64 exp) into
 // LDS (k-major) and stages the 16 x 128 slice of P.
 template <int KIND, int DM>
@@ -35,12 +37,12 @@ __global__ __launch_bounds__(KD_THREADS) void k_kgemm_f64_mfma(
     __syncthreads();
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
-    const int wm = wave & 3, wn = wave >> 2;
+    const int wm = wave & 1, wn = wave >> 1;
     const int64_t i0 = (int64_t)blockIdx.x * KD_BM;
     const int64_t c0 = (int64_t)blockIdx.y * KD_BN;
 
     const int trow = t & (KD_BM - 1);
-    const int pg = __builtin_amdgcn_readfirstlane(t >> 8);   // 0..3: which 4 of the 16 points
+    const int pg = __builtin_amdgcn_readfirstlane(t / KD_BM);   // 0..3: which 4 of the 16 points
     const int64_t gi = i0 + trow;
     const int64_t gic = gi < n ? gi : n - 1;
     float xi[DM];
@@ -55,7 +57,7 @@ __global__ __launch_bounds__(KD_THREADS) void k_kgemm_f64_mfma(
     // the next step's point records (wave-uniform) and P values are loaded while the
     // current step's MFMAs run
     float xj[4][DM];
-    double pv[2];
+    double pv[4];
     auto load = [&](int64_t j0) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -65,8 +67,8 @@ __global__ __launch_bounds__(KD_THREADS) void k_kgemm_f64_mfma(
             for (int k = 0; k < DM; ++k) xj[e][k] = xa[gjc * DM + k];
         }
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int64_t gj = j0 + (t & 15), gc = c0 + (t >> 4) + 64 * s;
+        for (int s = 0; s < 4; ++s) {
+            const int64_t gj = j0 + (t & 15), gc = c0 + (t >> 4) + 32 * s;
             pv[s] = (gj < n && gc < m) ? P[gj + gc * ldp] : 0.0;
         }
     };
@@ -85,7 +87,7 @@ __global__ __launch_bounds__(KD_THREADS) void k_kgemm_f64_mfma(
             As[p][trow] = (j0 + p < n) ? kentry64<KIND>(-0.5 * g * r2, kconst, tab) : 0.0;
         }
 #pragma unroll
-        for (int s = 0; s < 2; ++s) Bs[t & 15][(t >> 4) + 64 * s] = pv[s];
+        for (int s = 0; s < 4; ++s) Bs[t & 15][(t >> 4) + 32 * s] = pv[s];
         if (j0 + KD_BK < n) load(j0 + KD_BK);
         __syncthreads();
 #pragma unroll
