@@ -227,6 +227,8 @@ KernelOp kernel_op_of(const rr_precond& P) {
 void setup_operator(rr_precond& P, hipStream_t st, int products) {
     const rr_operator& A = P.op;
     const int64_t n = A.n;
+    // (an operator that only multiplies may be given any matrix: it reads it whole)
+    P.dense_sym = !is_kernel(A) && products == SETUP_ALL && dense_sym_ok(n, P.opts.prec != RR_PREC_FP64);
     if (is_kernel(A)) {
         const int dm = kernel_record_len(A.d);
         const bool mma = kernel_mma_ok(n, A.d);
@@ -252,16 +254,19 @@ void setup_operator(rr_precond& P, hipStream_t st, int products) {
             launch_kmma_records(kernel_op_of(P), P.rrec.ptr(), P.crec.ptr(), st);
         }
     } else if (P.opts.prec != RR_PREC_FP64) {
-        P.A32.reset(&P.alloc, (size_t)n * n * sizeof(float));
-        launch_copy_mat(DT_F64, A.A, A.lda, DT_F32, P.A32.ptr(), n, n, n, st);
+        // columns on 16-byte boundaries for the wide loads of the triangle's product
+        P.lda32 = P.dense_sym ? (n + 3) / 4 * 4 : n;
+        P.A32.reset(&P.alloc, (size_t)n * P.lda32 * sizeof(float));
+        launch_copy_mat(DT_F64, A.A, A.lda, DT_F32, P.A32.ptr(), P.lda32, n, n, st);
     }
 }
 
 int operator_part_count(const rr_precond& P) {
-    return is_kernel(P.op) ? kernel_matvec_blocks(P.n) : dense_matvec_blocks(P.n);
+    return is_kernel(P.op) || P.dense_sym ? kernel_matvec_blocks(P.n) : dense_matvec_blocks(P.n);
 }
 
 size_t operator_ws_doubles(const rr_precond& P) {
+    if (P.dense_sym) return dense_sym_ws_doubles(P.n);
     return is_kernel(P.op) ? kernel_matvec_ws_doubles(P.n, P.op.d, 2) : 0;
 }
 
@@ -273,11 +278,12 @@ int apply_operator(const rr_precond& P, const double* u, double mu, double* y, d
                              stop, st);
         return kernel_matvec_blocks(P.n);
     }
-    if (!fp64 && P.A32.ptr())
-        launch_dense_matvec(DT_F32, P.n, P.A32.ptr(), P.n, u, mu, y, dot_part, stop, st);
-    else
-        launch_dense_matvec(DT_F64, P.n, P.op.A, P.op.lda, u, mu, y, dot_part, stop, st);
-    return dense_matvec_blocks(P.n);
+    const bool f32 = !fp64 && P.A32.ptr();
+    const void* A = f32 ? P.A32.ptr() : (const void*)P.op.A;
+    const int64_t lda = f32 ? P.lda32 : P.op.lda;
+    if (P.dense_sym) launch_dense_matvec_sym(f32 ? DT_F32 : DT_F64, P.n, A, lda, u, mu, y, dot_part, kmv_ws, stop, st);
+    else launch_dense_matvec(f32 ? DT_F32 : DT_F64, P.n, A, lda, u, mu, y, dot_part, stop, st);
+    return operator_part_count(P);
 }
 
 void apply_operator_multi(const rr_precond& P, const double* U, int nr, double mu, double* Y,

@@ -182,7 +182,7 @@ struct Batch {
             if (fp64 || P.opts.prec == RR_PREC_FP64) launch_kernel_matmat_f64(k, muc, Pin, ldp, mc, Wout, n, st);
             else launch_kernel_matmat_bf16x6(k, muc, Pin, ldp, mc, Wout, n, kws.ptr(), kws.bytes(), st);
         } else {
-            if (!fp64 && P.A32.ptr()) gemm(false, false, n, mc, n, P.A32.ptr(), n, Pin, ldp, Wout, n, 1.0, 0.0, DT_F32);
+            if (!fp64 && P.A32.ptr()) gemm(false, false, n, mc, n, P.A32.ptr(), P.lda32, Pin, ldp, Wout, n, 1.0, 0.0, DT_F32);
             else gemm(false, false, n, mc, n, P.op.A, P.op.lda, Pin, ldp, Wout, n, 1.0, 0.0);
             launch_add_shift_cols(n, mc, muc, Pin, ldp, Wout, n, st);
         }

@@ -240,7 +240,7 @@ struct Builder {
         launch_copy_mat(odt, Om, n, DT_F64, Y, n, n, l, st);
         launch_scale_mat((double*)Y, n, n, l, mu, st);
         if (A16) gemm(DT_BF16, false, odt, false, n, l, n, A16, n, Om, n, (double*)Y, n, 1.0, 1.0);
-        else if (P.A32.ptr()) gemm(DT_F32, false, odt, false, n, l, n, P.A32.ptr(), n, Om, n, (double*)Y, n, 1.0, 1.0);
+        else if (P.A32.ptr()) gemm(DT_F32, false, odt, false, n, l, n, P.A32.ptr(), P.lda32, Om, n, (double*)Y, n, 1.0, 1.0);
         else gemm(DT_F64, false, odt, false, n, l, n, P.op.A, P.op.lda, Om, n, (double*)Y, n, 1.0, 1.0);
         check_launch();
     }

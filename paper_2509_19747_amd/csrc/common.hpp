@@ -70,6 +70,66 @@ RR_DEV float xor_pair_sum(float v) {
     return __builtin_bit_cast(float, r.x) + __builtin_bit_cast(float, r.y);
 }
 
+// v of lane l ^ M (M = 1, 2, 4 or 8) by DPP moves: within quads, within half rows
+// (mirror, then mirrored quads: l ^ 7 ^ 3) and rotated by half a row of 16.
+template <int M>
+RR_DEV uint32_t lane_xor(uint32_t v) {
+    static_assert(M == 1 || M == 2 || M == 4 || M == 8, "lane_xor: M must be 1, 2, 4 or 8");
+    if constexpr (M == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);
+    else if constexpr (M == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);
+    else if constexpr (M == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);
+    else return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+}
+template <int M>
+RR_DEV double lane_xor(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = lane_xor<M>((uint32_t)b), hi = lane_xor<M>((uint32_t)(b >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <int M>
+RR_DEV float lane_xor(float v) { return __builtin_bit_cast(float, lane_xor<M>(__builtin_bit_cast(uint32_t, v))); }
+
+// On lanes with l & 16 clear: a + (a of lane l ^ 16); else b + (b of lane l ^ 16).  One
+// row swap of the pair puts both terms of each lane's sum into the two registers.
+RR_DEV double swap16_sum(double a, double b) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+}
+RR_DEV float swap16_sum(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b),
+                                                    false, false);
+    // (a bit cast straight from a vector element reads element 0 with this compiler)
+    const uint32_t r0 = r[0], r1 = r[1];
+    return __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
+}
+
+// The same across the halves of the wave: lanes < 32 get a + (a of lane l ^ 32), the
+// others b + (b of lane l ^ 32).
+RR_DEV double swap32_sum(double a, double b) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+}
+// v of one lane (wave-uniform index), in scalar registers.
+RR_DEV double read_lane(double v, int l) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, l), hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), l);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// One step of a reduce-scatter: lanes with l & M clear keep the sums of v[0 .. N), the
+// others those of v[N .. 2 N).
+template <int M, typename T, int N>
+RR_DEV void lane_halve(const T (&v)[2 * N], T (&w)[N], int l) {
+    const bool b = l & M;
+#pragma unroll
+    for (int e = 0; e < N; ++e) w[e] = (b ? v[N + e] : v[e]) + lane_xor<M>(b ? v[e] : v[N + e]);
+}
+
 // DPP wave reduction towards lane 63.  One step on a float64 value (the same
 // DPP move on both halves; rows outside row_mask read 0 and keep their value).
 template <int CTRL, int ROWMASK>

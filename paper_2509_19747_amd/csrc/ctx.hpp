@@ -173,7 +173,9 @@ struct rr_precond {
     bool joint = false;
     rr::Alloc alloc;
     // operator-derived data
-    rr::DBuf A32;         // float32 copy of a dense A (FP32 / MIXED)
+    rr::DBuf A32;         // float32 copy of a dense A (FP32 / MIXED), leading dimension lda32
+    int64_t lda32 = 0;
+    bool dense_sym = false;   // products read the upper triangle of a stored A only
     rr::DBuf sqn;         // |x_i|^2 (kernel operators)
     rr::DBuf xa;          // padded point records (kernel operators)
     rr::DBuf rrec, crec;  // packed bf16 records of the MFMA matvec (float32-class handles)

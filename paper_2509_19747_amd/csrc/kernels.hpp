@@ -181,6 +181,19 @@ void launch_dense_matvec(int dta, int64_t n, const void* A, int64_t lda, const d
                          double mu, double* y, double* dot_part, const int32_t* stop,
                          hipStream_t st);
 
+// The same reading the upper triangle only (where dense_sym_ok: f32 if products with a
+// float32 matrix are among them), with a workspace of dense_sym_ws_doubles(n);
+// kernel_matvec_blocks(n) partials of u^T y.
+constexpr int64_t DENSE_SYM_MIN32 = 5632, DENSE_SYM_MIN64 = 4096;
+bool dense_sym_ok(int64_t n, bool f32);
+size_t dense_sym_ws_doubles(int64_t n);
+void launch_dense_matvec_sym(int dta, int64_t n, const void* A, int64_t lda, const double* u, double mu, double* y,
+                             double* dot_part, double* ws, const int32_t* stop, hipStream_t st);
+// The finish of a product whose partials lie in slots (k_ksym_mma's layout): y = scale
+// (sum of a row's slots) + mu u with kernel_matvec_blocks(n) partials of u^T y.
+void launch_slot_finish(int64_t n, int nb, int m, int S, int nr, const double* part, double scale, double mu,
+                        const double* u, double* y, double* dot_part, const int32_t* stop, hipStream_t st);
+
 // Kernel operator y = scale*K u + mu u with K from points (float32 or float64
 // evaluation, float64 accumulation), partials of u^T y.
 struct KernelOp {

@@ -154,58 +154,16 @@ struct KmmaWalk {
     }
 };
 
-// v of lane l ^ M (M = 1, 2, 4 or 8) by DPP moves: within quads, within half rows
-// (mirror, then mirrored quads: l ^ 7 ^ 3) and rotated by half a row of 16.
-template <int M>
-RR_DEV uint32_t lane_xor(uint32_t v) {
-    static_assert(M == 1 || M == 2 || M == 4 || M == 8, "lane_xor: M must be 1, 2, 4 or 8");
-    if constexpr (M == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);
-    else if constexpr (M == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);
-    else if constexpr (M == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);
-    else return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
-}
-template <int M>
-RR_DEV double lane_xor(double v) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = lane_xor<M>((uint32_t)b), hi = lane_xor<M>((uint32_t)(b >> 32));
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-template <int M>
-RR_DEV float lane_xor(float v) { return __builtin_bit_cast(float, lane_xor<M>(__builtin_bit_cast(uint32_t, v))); }
-
-// On lanes with l & 16 clear: a + (a of lane l ^ 16); else b + (b of lane l ^ 16).  One
-// row swap of the pair puts both terms of each lane's sum into the two registers.
-RR_DEV double swap16_sum(double a, double b) {
-    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
-    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
-    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
-           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
-}
-RR_DEV float swap16_sum(float a, float b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b),
-                                                    false, false);
-    // (a bit cast straight from a vector element reads element 0 with this compiler)
-    const uint32_t r0 = r[0], r1 = r[1];
-    return __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
-}
-
 // Sum over the 32 lanes of a half-wave of v[0..15] (reduce-scatter butterfly in a
 // fixed order): on return lanes 2e and 2e + 1 of the half hold the total of v[e].
-template <int M, typename T, int N>
-RR_DEV void kmma_halve(const T (&v)[2 * N], T (&w)[N], int l32) {
-    const bool b = l32 & M;
-#pragma unroll
-    for (int e = 0; e < N; ++e) w[e] = (b ? v[N + e] : v[e]) + lane_xor<M>(b ? v[e] : v[N + e]);
-}
 template <typename T>
 RR_DEV T kmma_rowsum16(const T (&v)[16], int l32) {
     T w8[8], w4[4], w2[2], w1[1];
 #pragma unroll
     for (int e = 0; e < 8; ++e) w8[e] = swap16_sum(v[e], v[8 + e]);
-    kmma_halve<8, T, 4>(w8, w4, l32);
-    kmma_halve<4, T, 2>(w4, w2, l32);
-    kmma_halve<2, T, 1>(w2, w1, l32);
+    lane_halve<8, T, 4>(w8, w4, l32);
+    lane_halve<4, T, 2>(w4, w2, l32);
+    lane_halve<2, T, 1>(w2, w1, l32);
     // lanes 2e and 2e + 1 add the same two partials in opposite order: equal sums
     return w1[0] + lane_xor<1>(w1[0]);
 }
@@ -844,6 +802,12 @@ void launch_kmma_records64(const KernelOp& op, double* xp, double* hd, hipStream
                                                                             hd);
 }
 
+void launch_slot_finish(int64_t n, int nb, int m, int S, int nr, const double* part, double scale, double mu,
+                        const double* u, double* y, double* dot_part, const int32_t* stop, hipStream_t st) {
+    k_ksym_mma_finish<<<dim3((unsigned)((n + 255) / 256), (unsigned)nr), 256 * KF_GROUPS, 0, st>>>(
+        n, KM_RB, nb, m, S, nr, part, scale, mu, u, y, dot_part, stop);
+}
+
 void launch_kernel_matvec_mma64(const KernelOp& op, const double* u, int nr, double mu, double* y,
                                 double* dot_part, double* ws, const int32_t* stop, hipStream_t st) {
     const KmmaPlan p = kmma_plan(op.n);
@@ -867,9 +831,7 @@ void launch_kernel_matvec_mma64(const KernelOp& op, const double* u, int nr, dou
 #undef KM64D
 #undef KM64
     }
-    k_ksym_mma_finish<<<dim3((unsigned)((op.n + 255) / 256), (unsigned)nr), 256 * KF_GROUPS, 0, st>>>(op.n, KM_RB, p.nb, p.m, p.S, nr, ws,
-                                                                      op.scale, mu, u, y, dot_part,
-                                                                      stop);
+    launch_slot_finish(op.n, p.nb, p.m, p.S, nr, ws, op.scale, mu, u, y, dot_part, stop, st);
 }
 
 template <int KIND, int NR, typename T>
@@ -927,9 +889,7 @@ void launch_kernel_matvec_mma(const KernelOp& op, const double* u, int nr, doubl
         if (op.kind == 1) { KMD(1) } else { KMD(2) }
 #undef KMD
     }
-    k_ksym_mma_finish<<<dim3((unsigned)((op.n + 255) / 256), (unsigned)nr), 256 * KF_GROUPS, 0, st>>>(op.n, KM_RB, p.nb, p.m, p.S, nr, ws,
-                                                                      op.scale, mu, u, y, dot_part,
-                                                                      stop);
+    launch_slot_finish(op.n, p.nb, p.m, p.S, nr, ws, op.scale, mu, u, y, dot_part, stop, st);
 }
 
 // ------------------------------------------------------------------ grouped

@@ -101,6 +101,31 @@ def test_kernel_matvec_plan_edges(kind, n, d):
             assert np.array_equal(y, Y[:, q]), (prec, q)
 
 
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,pad", [(4095, 0), (4096, 0), (4097, 0), (5632, 0), (5633, 3), (5889, 1), (6400, 2)])
+def test_dense_solve_large_blocks(n, pad, prec):
+    """Stored operators on both sides of the sizes from which products read the upper
+    triangle only (ragged and whole last blocks, columns on and off 16-byte boundaries):
+    the solution's residual formed with the whole matrix."""
+    import torch
+    from paper_2509_19747_amd import binding as rb
+    g = torch.Generator(device="cuda").manual_seed(n)
+    G = torch.randn(n, 48, device="cuda", dtype=torch.float64, generator=g)
+    A = torch.zeros(n, n + pad, device="cuda", dtype=torch.float64)
+    A[:, :n] = G @ G.T / n
+    A[:, :n].diagonal().add_(torch.rand(n, device="cuda", dtype=torch.float64, generator=g) * 0.02)
+    st = rb.rr_operator(kind=rb.OP_DENSE, n=n, A=A.data_ptr(), lda=n + pad, pts=None, d=0, kconst=0.0, scale=1.0)
+    op = rb.Operator(st, (A,))
+    mu, tol = 1e-2, 1e-10
+    P = rr.build_precond(op, [mu], l=64, seed=5, prec=prec)
+    b = torch.randn(n, device="cuda", dtype=torch.float64, generator=g)
+    x, info = P.solve(b, tol=tol)
+    res = b - A[:, :n] @ x - mu * x
+    # the stop test is on the recurrence or the restart's own residual: both within
+    # rounding (about n eps cond) of this one
+    assert float(res.norm() / b.norm()) <= 1.5 * tol
+
+
 @pytest.mark.parametrize("kind", [rr.OP_RBF, rr.OP_MATERN32])
 @pytest.mark.parametrize("n,d,nr", [(5000, 16, 1), (5000, 16, 2), (4100, 5, 3), (3001, 20, 5),
                                     (4500, 8, 8), (2600, 4, 13)])
