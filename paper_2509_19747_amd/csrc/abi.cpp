@@ -301,8 +301,10 @@ void apply_operator_multi(const rr_precond& P, const double* U, int nr, double m
 }
 
 int apply_projected(const rr_precond& P, const double* Kc, const double* r, double rcoef, double* z,
-                    double* c_part, double* d, double* rz_part, const int32_t* stop, hipStream_t st) {
+                    double* c_part, double* d, double* rz_part, const int32_t* stop, hipStream_t st,
+                    const double* rr_part, int count, CgState* cg) {
     if (P.basisless) {
+        if (cg) launch_scal_rr(rr_part, count, cg, st);
         // z = rcoef r + Y Kr Y^T r with Y = A_mu Omega (Kc holds Kr^T)
         const KernelOp k = kernel_op_of(P);
         const bool f64 = P.opts.prec == RR_PREC_FP64;
@@ -314,7 +316,8 @@ int apply_projected(const rr_precond& P, const double* Kc, const double* r, doub
         return kblock_cols_blocks(P.n);
     }
     const int nch = gemv_t_chunks(P.n, P.kb);
-    launch_gemv_t(P.n, P.kb, P.Qb.as<double>(), P.n, r, c_part, nch, stop, st);
+    if (cg) launch_gemv_t_rr(P.n, P.kb, P.Qb.as<double>(), P.n, r, c_part, nch, rr_part, count, cg, st);
+    else launch_gemv_t(P.n, P.kb, P.Qb.as<double>(), P.n, r, c_part, nch, stop, st);
     launch_core_apply(P.kb, Kc, P.kb, c_part, nch, d, stop, st);
     launch_qd(P.n, P.kb, P.Qb.as<double>(), P.n, d, r, rcoef, z, rz_part, stop, st);
     return qd_blocks(P.n);

@@ -186,6 +186,27 @@ RR_DEV double block_sum_array(const double* __restrict__ a, int count, double* s
     return block_sum(v, scratch);
 }
 
+// block_sum_array of a block of 1024 threads formed by one of 256: the same terms in the
+// same order, each wave taking four waves' parts.  `scratch` holds 16 doubles.
+RR_DEV double block_sum_array_1024(const double* __restrict__ a, int count, double* scratch) {
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i = threadIdx.x; i < count; i += 1024)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (i + 256 * q < count) v[q] += a[i + 256 * q];
+    const int w = threadIdx.x / WAVE;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        v[q] = wave_sum(v[q]);
+        if ((threadIdx.x & (WAVE - 1)) == 0) scratch[4 * q + w] = v[q];
+    }
+    __syncthreads();
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s += scratch[i];
+    return s;
+}
+
 // -------------------------------------------------------- counter-based RNG
 // SplitMix64 (Steele, Lea, Flood, OOPSLA 2014): word k of the stream seeded
 // with s is the 64-bit finaliser applied to s + (k+1) * 0x9E3779B97F4A7C15.

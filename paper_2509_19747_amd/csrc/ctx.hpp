@@ -228,9 +228,12 @@ enum { SETUP_ALL = 0, SETUP_PRODUCTS, SETUP_WORK, SETUP_F64 };
 void setup_operator(rr_precond& P, hipStream_t st, int products = SETUP_ALL);
 size_t operator_ws_doubles(const rr_precond& P);
 
-// z = rcoef*r + Qb (Kc (Qb^T r)), with partials of r^T z.  Returns #partials.
+// z = rcoef*r + Qb (Kc (Qb^T r)), with partials of r^T z.  Returns #partials.  rr_part,
+// count, cg: also the iteration's stop test on the residual's partials (launch_scal_rr),
+// which stop (the state's flag) then follows.
 int apply_projected(const rr_precond& P, const double* Kc, const double* r, double rcoef, double* z,
-                    double* c_part, double* d, double* rz_part, const int32_t* stop, hipStream_t st);
+                    double* c_part, double* d, double* rz_part, const int32_t* stop, hipStream_t st,
+                    const double* rr_part = nullptr, int count = 0, rr::CgState* cg = nullptr);
 // Two vectors at once (R, Z: n x 2, leading dimension n), each with its own core:
 // Z[:, q] = rc_q R[:, q] + Q K_q Q^T R[:, q].  c_part: 2 * nchunks * kb doubles,
 // d: 2 * kb, rz_part: 2 * qd_blocks(n).

@@ -13,7 +13,8 @@ enum Dtype { DT_F64 = 0, DT_F32 = 1, DT_BF16 = 2 };
 // scalars they need and return immediately once `stop` is non-zero, so a batch
 // of iterations launched ahead of a host check becomes a no-op past the exit.
 struct CgState {
-    double alpha, beta, rho, rr, pw, target2;
+    double rho[2];      // r^T z of iteration i in rho[i & 1] (i = iters)
+    double rr, target2;
     int32_t stop;       // 0 running, 1 reached target (restart/converged), 2 breakdown, 3 maxit
     int32_t iters;
     int32_t maxit;
@@ -349,6 +350,9 @@ int gemv_t_chunks(int64_t n, int64_t k);
 int64_t gemv_t_rows_per_chunk_of(int64_t n, int64_t k);   // rows of each of those chunks
 void launch_gemv_t(int64_t n, int64_t k, const double* Q, int64_t ldq, const double* r,
                    double* c_part, int nchunks, const int32_t* stop, hipStream_t st);
+// The same with launch_scal_rr(part, count, s) as a block beside those of the product.
+void launch_gemv_t_rr(int64_t n, int64_t k, const double* Q, int64_t ldq, const double* r, double* c_part,
+                      int nchunks, const double* part, int count, CgState* s, hipStream_t st);
 // nr = 1 or 2 vectors (R: n x nr, leading dimension ldr); vector q's partials at
 // c_part + q * nchunks * k.
 void launch_gemv_t_multi(int nr, int64_t n, int64_t k, const double* Q, int64_t ldq, const double* R,
@@ -389,20 +393,20 @@ void launch_normalize(int64_t n, double* v, const double* src, const double* par
 
 // ----------------------------------------------------------- CG updates
 int vec_blocks(int64_t n);
-// x += alpha p; r -= alpha w; partial ||r||^2
+// x += alpha p; r -= alpha w with alpha = r^T z / (sum of pw_part); partial ||r||^2 into
+// rr_part (not pw_part's memory: every block reads all of that)
 void launch_xr_update(int64_t n, double* x, double* r, const double* p, const double* w,
-                      CgState* s, double* rr_part, hipStream_t st);
-// p = z + beta p
-void launch_p_update(int64_t n, const double* z, double* p, const CgState* s, hipStream_t st);
+                      CgState* s, const double* pw_part, int count, double* rr_part, hipStream_t st);
+// p = z + beta p with beta from the sum of rz_part
+void launch_p_update(int64_t n, const double* z, double* p, CgState* s, const double* rz_part, int count,
+                     hipStream_t st);
 // r = b - w, partial ||r||^2
 void launch_residual(int64_t n, const double* b, const double* w, double* r, double* rr_part,
                      hipStream_t st);
 void launch_copy_vec(int64_t n, const double* src, double* dst, hipStream_t st);
 void launch_dot_part(int64_t n, const double* a, const double* b, double* part, hipStream_t st);
 // single-block scalar steps
-void launch_scal_alpha(const double* part, int count, CgState* s, hipStream_t st);
 void launch_scal_rr(const double* part, int count, CgState* s, hipStream_t st);
-void launch_scal_beta(const double* part, int count, CgState* s, hipStream_t st);
 void launch_scal_set(const double* part, int count, double* out, hipStream_t st);  // out = sum
 void launch_state_init(CgState* s, const double* rz_part, int rz_count, double target2,
                        int32_t maxit, int32_t iters, double* hist, int32_t hist_cap,

@@ -601,6 +601,42 @@ void launch_gemv_t(int64_t n, int64_t k, const double* Q, int64_t ldq, const dou
     launch_gemv_t_multi(1, n, k, Q, ldq, r, n, c_part, nchunks, stop, st);
 }
 
+// The step after the residual's update: ||r||^2 of the iteration and the stop test.
+RR_DEV void cg_rr_step(double rr, CgState* s) {
+    s->rr = rr;
+    const int it = s->iters + 1;
+    s->iters = it;
+    if (s->hist && it < s->hist_cap) s->hist[it] = rr;
+    if (!isfinite(rr)) s->stop = STOP_BREAKDOWN;
+    else if (rr <= s->target2) s->stop = STOP_TARGET;
+    else if (it >= s->maxit) s->stop = STOP_MAXIT;
+}
+// Q^T r does not need that step's result: block 0 takes it while the others form the
+// product (a launch less in every iteration; once the step has stopped the cycle the
+// product is of no use and its partials are not read).
+__global__ __launch_bounds__(GT_THREADS) void k_gemv_t_rr(int64_t n, int64_t k, const double* __restrict__ Q,
+                                                          int64_t ldq, const double* __restrict__ r,
+                                                          double* __restrict__ c_part, int nchunks,
+                                                          int64_t rows_per_chunk, const double* __restrict__ part,
+                                                          int count, CgState* s) {
+    static_assert(GT_THREADS == 256, "block_sum_array_1024");
+    __shared__ double sc[16];
+    if (s->stop) return;
+    if (blockIdx.x == 0) {
+        const double rr = block_sum_array_1024(part, count, sc);
+        if (threadIdx.x == 0) cg_rr_step(rr, s);
+        return;
+    }
+    const int b = (int)blockIdx.x - 1, nx = (int)((k + GT_COLS - 1) / GT_COLS);
+    gemv_t_block<1>(b % nx, b / nx, n, k, Q, ldq, r, 0, c_part, nchunks, rows_per_chunk);
+}
+void launch_gemv_t_rr(int64_t n, int64_t k, const double* Q, int64_t ldq, const double* r, double* c_part,
+                      int nchunks, const double* part, int count, CgState* s, hipStream_t st) {
+    const unsigned grid = 1 + (unsigned)((k + GT_COLS - 1) / GT_COLS) * nchunks;
+    k_gemv_t_rr<<<grid, GT_THREADS, 0, st>>>(n, k, Q, ldq, r, c_part, nchunks, gemv_t_rows_per_chunk(n, k), part,
+                                             count, s);
+}
+
 // d_i = sum_j Kc[j, i] c_j with c_j = sum_ch c_part[ch*k + j] (Kc symmetric).
 // blockIdx.y = column q of a pair (core K0 or K1, its own c_part and d slices).
 // Each thread finishes the c_j of its own j (partials added in chunk order) and
@@ -791,14 +827,34 @@ int vec_blocks(int64_t n) {
     return (int)g;
 }
 
+// The scalars of an iteration are sums of a few hundred partials: every block of the
+// vector step that needs one forms it itself, in the order of a block of 1024 threads
+// (a launch of one block for it costs 4 us at n = 2000, this 1 to 2), and block 0 keeps
+// it.  The stop flag is read by one thread for the block: block 0 of the same launch may
+// set it while others start.
+RR_DEV bool cg_sum(const double* __restrict__ part, int count, const CgState* s, double* sum) {
+    __shared__ double sc[16];
+    __shared__ int32_t stop;
+    if (threadIdx.x == 0) stop = s->stop;
+    *sum = block_sum_array_1024(part, count, sc);
+    return stop == STOP_NONE;
+}
+
 __global__ __launch_bounds__(VB) void k_xr_update(int64_t n, double* __restrict__ x,
                                                   double* __restrict__ r,
                                                   const double* __restrict__ p,
                                                   const double* __restrict__ w, CgState* s,
+                                                  const double* __restrict__ pw_part, int count,
                                                   double* __restrict__ rr_part) {
     __shared__ double sc[VB / WAVE];
-    if (s->stop) return;
-    const double a = s->alpha;
+    double pw;
+    const double rho = s->rho[s->iters & 1];
+    if (!cg_sum(pw_part, count, s, &pw)) return;
+    if (!(pw > 0.0) || !isfinite(pw)) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) s->stop = STOP_BREAKDOWN;
+        return;
+    }
+    const double a = rho / pw;
     double acc = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * VB + threadIdx.x; i < n; i += (int64_t)gridDim.x * VB) {
         x[i] = fma(a, p[i], x[i]);
@@ -810,19 +866,31 @@ __global__ __launch_bounds__(VB) void k_xr_update(int64_t n, double* __restrict_
     if (threadIdx.x == 0) rr_part[blockIdx.x] = acc;
 }
 void launch_xr_update(int64_t n, double* x, double* r, const double* p, const double* w,
-                      CgState* s, double* rr_part, hipStream_t st) {
-    k_xr_update<<<vec_blocks(n), VB, 0, st>>>(n, x, r, p, w, s, rr_part);
+                      CgState* s, const double* pw_part, int count, double* rr_part, hipStream_t st) {
+    k_xr_update<<<vec_blocks(n), VB, 0, st>>>(n, x, r, p, w, s, pw_part, count, rr_part);
 }
 
+// (the old r^T z and the new one lie in different places: other blocks still read it)
 __global__ __launch_bounds__(VB) void k_p_update(int64_t n, const double* __restrict__ z,
-                                                 double* __restrict__ p, const CgState* s) {
-    if (s->stop) return;
-    const double b = s->beta;
+                                                 double* __restrict__ p, CgState* s,
+                                                 const double* __restrict__ rz_part, int count) {
+    double rz;
+    const int it = s->iters;
+    const double rho = s->rho[(it - 1) & 1];
+    if (!cg_sum(rz_part, count, s, &rz)) return;
+    const bool bad = !(rz > 0.0) || !isfinite(rz);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (bad) s->stop = STOP_BREAKDOWN;
+        else s->rho[it & 1] = rz;
+    }
+    if (bad) return;
+    const double b = rz / rho;
     for (int64_t i = (int64_t)blockIdx.x * VB + threadIdx.x; i < n; i += (int64_t)gridDim.x * VB)
         p[i] = fma(b, p[i], z[i]);
 }
-void launch_p_update(int64_t n, const double* z, double* p, const CgState* s, hipStream_t st) {
-    k_p_update<<<vec_blocks(n), VB, 0, st>>>(n, z, p, s);
+void launch_p_update(int64_t n, const double* z, double* p, CgState* s, const double* rz_part, int count,
+                     hipStream_t st) {
+    k_p_update<<<vec_blocks(n), VB, 0, st>>>(n, z, p, s, rz_part, count);
 }
 
 __global__ __launch_bounds__(VB) void k_residual(int64_t n, const double* __restrict__ b,
@@ -867,56 +935,14 @@ void launch_dot_part(int64_t n, const double* a, const double* b, double* part, 
 }
 
 // ----------------------------------------------------- scalar steps
-__global__ void k_scal_alpha(const double* __restrict__ part, int count, CgState* s) {
-    __shared__ double sc[16];
-    if (s->stop) return;
-    const double pw = block_sum_array(part, count, sc);
-    if (threadIdx.x == 0) {
-        s->pw = pw;
-        if (!(pw > 0.0) || !isfinite(pw)) {
-            s->stop = STOP_BREAKDOWN;
-        } else {
-            s->alpha = s->rho / pw;
-        }
-    }
-}
-void launch_scal_alpha(const double* part, int count, CgState* s, hipStream_t st) {
-    k_scal_alpha<<<1, 1024, 0, st>>>(part, count, s);
-}
-
 __global__ void k_scal_rr(const double* __restrict__ part, int count, CgState* s) {
     __shared__ double sc[16];
     if (s->stop) return;
     const double rr = block_sum_array(part, count, sc);
-    if (threadIdx.x == 0) {
-        s->rr = rr;
-        const int it = s->iters + 1;
-        s->iters = it;
-        if (s->hist && it < s->hist_cap) s->hist[it] = rr;
-        if (!isfinite(rr)) s->stop = STOP_BREAKDOWN;
-        else if (rr <= s->target2) s->stop = STOP_TARGET;
-        else if (it >= s->maxit) s->stop = STOP_MAXIT;
-    }
+    if (threadIdx.x == 0) cg_rr_step(rr, s);
 }
 void launch_scal_rr(const double* part, int count, CgState* s, hipStream_t st) {
     k_scal_rr<<<1, 1024, 0, st>>>(part, count, s);
-}
-
-__global__ void k_scal_beta(const double* __restrict__ part, int count, CgState* s) {
-    __shared__ double sc[16];
-    if (s->stop) return;
-    const double rz = block_sum_array(part, count, sc);
-    if (threadIdx.x == 0) {
-        if (!(rz > 0.0) || !isfinite(rz)) {
-            s->stop = STOP_BREAKDOWN;
-        } else {
-            s->beta = rz / s->rho;
-            s->rho = rz;
-        }
-    }
-}
-void launch_scal_beta(const double* part, int count, CgState* s, hipStream_t st) {
-    k_scal_beta<<<1, 1024, 0, st>>>(part, count, s);
 }
 
 __global__ void k_scal_set(const double* __restrict__ part, int count, double* out) {
@@ -934,10 +960,7 @@ __global__ void k_state_init(CgState* s, const double* __restrict__ rz_part, int
     __shared__ double sc[16];
     const double rz = block_sum_array(rz_part, rz_count, sc);
     if (threadIdx.x == 0) {
-        s->alpha = 0.0;
-        s->beta = 0.0;
-        s->rho = rz;
-        s->pw = 0.0;
+        s->rho[iters & 1] = rz;
         s->target2 = target2;
         s->iters = iters;
         s->maxit = maxit;

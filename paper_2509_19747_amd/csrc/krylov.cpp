@@ -158,13 +158,11 @@ struct Gen {
         CgState* cs = cgs.as<CgState>();
         const int32_t* stop = &cs->stop;
         op(p.as<double>(), w.as<double>(), stop);
-        launch_dot_part_stop(n, p.as<double>(), w.as<double>(), vpart.as<double>(), stop, st);
-        launch_scal_alpha(vpart.as<double>(), vec_blocks(n), cs, st);
-        launch_xr_update(n, y.as<double>(), r.as<double>(), p.as<double>(), w.as<double>(), cs, vpart.as<double>(),
-                         st);
+        launch_dot_part_stop(n, p.as<double>(), w.as<double>(), rzp.as<double>(), stop, st);
+        launch_xr_update(n, y.as<double>(), r.as<double>(), p.as<double>(), w.as<double>(), cs, rzp.as<double>(),
+                         vec_blocks(n), vpart.as<double>(), st);
         launch_scal_rr(vpart.as<double>(), vec_blocks(n), cs, st);
-        launch_scal_beta(vpart.as<double>(), vec_blocks(n), cs, st);
-        launch_p_update(n, r.as<double>(), p.as<double>(), cs, st);
+        launch_p_update(n, r.as<double>(), p.as<double>(), cs, vpart.as<double>(), vec_blocks(n), st);
         st = keep;
     }
 

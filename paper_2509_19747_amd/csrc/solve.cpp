@@ -3,12 +3,12 @@
 //
 // One iteration (Hestenes-Stiefel order):
 //   w = A_mu p, p^T w        (operator kernel, fused dot partials)
-//   alpha = rho / p^T w       (one-block scalar kernel)
-//   x += alpha p; r -= alpha w; ||r||^2
-//   stop test on ||r|| (device flag: every later kernel of the batch is a no-op)
+//   alpha = rho / p^T w; x += alpha p; r -= alpha w; ||r||^2   (one kernel)
+//   stop test on ||r|| (device flag: every later kernel of the batch is a no-op), a
+//   block of the first kernel of
 //   z = r + Q (K (Q^T r)), r^T z   (eq. g_randrand_explicit with the refined
 //                                   projector folded into K)
-//   beta = r^T z / rho; p = z + beta p
+//   beta = r^T z / rho; p = z + beta p   (one kernel)
 // The host launches `check_every` iterations at a time (optionally as one
 // replayed hipGraph) and reads the 8-byte state once per batch.  At every
 // restart the residual is recomputed from x, with the float64 operator when
@@ -116,17 +116,16 @@ struct Solver {
         double* w = W.w.as<double>();
         const int np = apply_operator(P, p, mu, w, W.op_part.as<double>(), W.kws.as<double>(), false,
                                       stop, st);
-        launch_scal_alpha(W.op_part.as<double>(), np, s, st);
-        launch_xr_update(n, x, r, p, w, s, W.rr_part.as<double>(), st);
-        launch_scal_rr(W.rr_part.as<double>(), vec_blocks(n), s, st);
+        double* rrp = W.rr_part.as<double>();
+        launch_xr_update(n, x, r, p, w, s, W.op_part.as<double>(), np, rrp, st);
         if (P.l > 0) {
             const int nz = apply_projected(P, Kc, r, 1.0, W.z.as<double>(), W.c_part.as<double>(),
-                                           W.d.as<double>(), W.rz_part.as<double>(), stop, st);
-            launch_scal_beta(W.rz_part.as<double>(), nz, s, st);
-            launch_p_update(n, W.z.as<double>(), p, s, st);
+                                           W.d.as<double>(), W.rz_part.as<double>(), stop, st, rrp,
+                                           vec_blocks(n), s);
+            launch_p_update(n, W.z.as<double>(), p, s, W.rz_part.as<double>(), nz, st);
         } else {
-            launch_scal_beta(W.rr_part.as<double>(), vec_blocks(n), s, st);
-            launch_p_update(n, r, p, s, st);
+            launch_scal_rr(rrp, vec_blocks(n), s, st);
+            launch_p_update(n, r, p, s, rrp, vec_blocks(n), st);
         }
     }
 };

@@ -410,6 +410,38 @@ def test_solve_fp64_matches_oracle(dense_small, l, use_graph):
     assert np.linalg.norm(x - xs) / np.linalg.norm(xs) <= 10 * tol * cond
 
 
+@pytest.mark.parametrize("n", [3, 127, 257, 1023, 2047, 2048, 2051, 3333])
+def test_cg_scalar_sums(n):
+    """The iteration's scalars (sums of partials formed by every block of the next vector
+    step): the residual history of an unpreconditioned solve against conjugate gradients
+    in float64, with 2 to 1667 partials of p^T A p and 1 to 4 of ||r||^2, and a
+    preconditioned solve's solution."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    k = min(n, 32)
+    G = torch.randn(n, k, device="cuda", dtype=torch.float64, generator=g)
+    A = (G @ G.T / n).contiguous()
+    b = torch.randn(n, device="cuda", dtype=torch.float64, generator=g)
+    mu, its = 0.5, 6
+    x, r, p, hist = torch.zeros_like(b), b.clone(), b.clone(), [1.0]
+    for _ in range(its):
+        w = A @ p + mu * p
+        rr0 = r @ r
+        alpha = rr0 / (p @ w)
+        x, r = x + alpha * p, r - alpha * w
+        hist.append(float(r.norm() / b.norm()))
+        p = r + (r @ r) / rr0 * p
+    h = np.zeros(its + 2)
+    P = rr.build_precond(rr.dense_operator(A), [mu], l=0, prec="fp64")
+    xg, info = P.solve(b, tol=1e-12, restart_eta=1e-13, maxit=its, history=h, ok=(rr.RR_OK, rr.RR_ENOCONV))
+    m = min(info["iters"], its)
+    # rounding of six iterations at condition numbers below 100
+    for i in range(m + 1):
+        assert abs(h[i] - hist[i]) <= 1e-12 + 1e-9 * hist[i], i
+    P = rr.build_precond(rr.dense_operator(A), [mu], l=min(n // 3, 16), seed=1, prec="fp64")
+    xg, info = P.solve(b, tol=1e-10)
+    assert float((b - A @ xg - mu * xg).norm() / b.norm()) <= 1.5e-10
+
+
 def test_solve_graph_equals_eager_bitwise(dense_small):
     prob, op, kop, A = dense_small
     P = rr.build_precond(rr.dense_operator(A), prob.mus, l=prob.l, seed=prob.omega_seed)
