@@ -847,8 +847,20 @@ __global__ __launch_bounds__(VB) void k_xr_update(int64_t n, double* __restrict_
                                                   const double* __restrict__ pw_part, int count,
                                                   double* __restrict__ rr_part) {
     __shared__ double sc[VB / WAVE];
-    double pw;
-    const double rho = s->rho[s->iters & 1];
+    // the first four elements of a thread (all of them up to 2048 blocks) are loaded
+    // before the sum's wait
+    const int64_t i0 = (int64_t)blockIdx.x * VB + threadIdx.x, step = (int64_t)gridDim.x * VB;
+    double pv[4], wv[4], xv[4], rv[4], pw;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int64_t i = i0 + k * step < n ? i0 + k * step : n - 1;
+        pv[k] = p[i];
+        wv[k] = w[i];
+        xv[k] = x[i];
+        rv[k] = r[i];
+    }
+    const double rho0 = s->rho[0], rho1 = s->rho[1];
+    const double rho = s->iters & 1 ? rho1 : rho0;
     if (!cg_sum(pw_part, count, s, &pw)) return;
     if (!(pw > 0.0) || !isfinite(pw)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) s->stop = STOP_BREAKDOWN;
@@ -856,7 +868,15 @@ __global__ __launch_bounds__(VB) void k_xr_update(int64_t n, double* __restrict_
     }
     const double a = rho / pw;
     double acc = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * VB + threadIdx.x; i < n; i += (int64_t)gridDim.x * VB) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (i0 + k * step < n) {
+            x[i0 + k * step] = fma(a, pv[k], xv[k]);
+            const double ri = fma(-a, wv[k], rv[k]);
+            r[i0 + k * step] = ri;
+            acc = fma(ri, ri, acc);
+        }
+    for (int64_t i = i0 + 4 * step; i < n; i += step) {
         x[i] = fma(a, p[i], x[i]);
         const double ri = fma(-a, w[i], r[i]);
         r[i] = ri;
@@ -874,9 +894,17 @@ void launch_xr_update(int64_t n, double* x, double* r, const double* p, const do
 __global__ __launch_bounds__(VB) void k_p_update(int64_t n, const double* __restrict__ z,
                                                  double* __restrict__ p, CgState* s,
                                                  const double* __restrict__ rz_part, int count) {
-    double rz;
+    const int64_t i0 = (int64_t)blockIdx.x * VB + threadIdx.x, step = (int64_t)gridDim.x * VB;
+    double zv[4], pv[4], rz;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int64_t i = i0 + k * step < n ? i0 + k * step : n - 1;
+        zv[k] = z[i];
+        pv[k] = p[i];
+    }
     const int it = s->iters;
-    const double rho = s->rho[(it - 1) & 1];
+    const double rho0 = s->rho[0], rho1 = s->rho[1];
+    const double rho = it & 1 ? rho0 : rho1;
     if (!cg_sum(rz_part, count, s, &rz)) return;
     const bool bad = !(rz > 0.0) || !isfinite(rz);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -885,8 +913,10 @@ __global__ __launch_bounds__(VB) void k_p_update(int64_t n, const double* __rest
     }
     if (bad) return;
     const double b = rz / rho;
-    for (int64_t i = (int64_t)blockIdx.x * VB + threadIdx.x; i < n; i += (int64_t)gridDim.x * VB)
-        p[i] = fma(b, p[i], z[i]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (i0 + k * step < n) p[i0 + k * step] = fma(b, pv[k], zv[k]);
+    for (int64_t i = i0 + 4 * step; i < n; i += step) p[i] = fma(b, p[i], z[i]);
 }
 void launch_p_update(int64_t n, const double* z, double* p, CgState* s, const double* rz_part, int count,
                      hipStream_t st) {
