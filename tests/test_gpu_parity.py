@@ -390,6 +390,13 @@ def test_build_fp64_triangular_inverse_widths(n, l):
     assert np.abs(g["Q"].T @ g["Q"] - np.eye(l)).max() < 1e-12
 
 
+@pytest.mark.parametrize("n,l", [(1100, 513), (1700, 768), (1800, 769), (2200, 1024), (2300, 1025)])
+def test_build_fp64_wide_triangular_inverse(n, l):
+    """The same for the widths of the twelve- and sixteen-slot inverses and past them,
+    their k steps whole and ragged."""
+    test_build_fp64_triangular_inverse_widths(n, l)
+
+
 @pytest.mark.parametrize("l", [0, 45])
 @pytest.mark.parametrize("use_graph", [False, True])
 def test_solve_fp64_matches_oracle(dense_small, l, use_graph):
