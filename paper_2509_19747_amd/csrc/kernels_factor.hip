@@ -19,14 +19,16 @@ constexpr int CH_NB = 32;
 
 // One block row of the blocked Cholesky in a single launch of 64-thread blocks:
 // every block factors the kb x kb diagonal block A11 = R11^T R11 (identical
-// arithmetic in every block), then solves R11^T X = A12 for its 64 columns of the
-// row panel.  Lane j holds column j of A11 in registers; row k of R11 is shared
-// through LDS once it is formed, so the inner loops only read LDS broadcasts.
+// arithmetic in every block) and solves R11^T X = A12 for its 64 columns of the
+// row panel, both row by row: lane j holds column j of A11 and its column of A12 in
+// registers, row k of R11 is read lane by lane into scalars (readlane) and serves the
+// updates of both, all independent of one another, so a step's chain is a square root
+// and a division: 24.7 us a launch (with row k shared through LDS and the solve behind the
+// factorisation, each entry's sum a chain of its own: 30.3).
 // Block 0 writes R11 back (zeros below the diagonal) and raises the status word
 // when a pivot is not positive and finite.
 __global__ __launch_bounds__(64) void k_chol_panel(double* A, int64_t lda, int kb, int64_t rest,
                                                    int32_t* status) {
-    __shared__ double rk[CH_NB][CH_NB + 1];   // rk[k][i] = R11(k, i), i >= k
     if (*status) return;
     const int t = threadIdx.x;
     double col[CH_NB];
@@ -41,30 +43,23 @@ __global__ __launch_bounds__(64) void k_chol_panel(double* A, int64_t lda, int k
 #pragma unroll
     for (int k = 0; k < CH_NB; ++k) {
         if (k >= kb) continue;   // uniform
-        const double dkk = __shfl(col[k], k);
+        const double dkk = read_lane(col[k], k);
         const bool ok = dkk > 0.0 && isfinite(dkk);
         bad = bad || !ok;
         const double piv = ok ? sqrt(dkk) : 1.0;
         const double rkt = (t == k) ? piv : (t > k ? col[k] / piv : 0.0);
         if (t >= k) col[k] = rkt;
-        if (t < CH_NB) rk[k][t] = rkt;
-        __syncthreads();
+        x[k] = x[k] / piv;
 #pragma unroll
         for (int i = k + 1; i < CH_NB; ++i) {
-            const double rki = rk[k][i];
-            if (i <= t && t < kb) col[i] = fma(-rki, rkt, col[i]);
+            const double rki = read_lane(rkt, i);
+            if (i < kb) {   // (uniform)
+                col[i] = fma(-rki, rkt, col[i]);   // (lanes t < i: not used)
+                x[i] = fma(-rki, x[k], x[i]);
+            }
         }
     }
-    __syncthreads();
     if (jc < rest) {
-#pragma unroll
-        for (int i = 0; i < CH_NB; ++i) {
-            if (i >= kb) continue;
-            double s = x[i];
-#pragma unroll
-            for (int k = 0; k < i; ++k) s = fma(-rk[k][i], x[k], s);
-            x[i] = s / rk[i][i];
-        }
 #pragma unroll
         for (int i = 0; i < CH_NB; ++i)
             if (i < kb) A[i + (kb + jc) * lda] = x[i];
