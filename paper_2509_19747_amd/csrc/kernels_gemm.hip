@@ -7,7 +7,10 @@
 // tiles each, 16 float64 accumulators per lane); block tile 64 x 64; k step 16.
 // The small tile keeps registers low so several blocks share a compute unit: the
 // float64 MFMA pipe needs several resident waves per SIMD to stay busy.
-// The next k step's tiles are loaded into registers while the current one is
+// The vector ALU does not overlap the float64 MFMA: a step's loads go by offsets fixed
+// for the block from a scalar base (with bounds and 64-bit addresses formed for each:
+// 49.9 TF/s at 32768 x 1024 x 1024, so 61.0; the transposed product 48.7, 59.5).
+// The k steps' tiles are loaded into registers while earlier ones are
 // multiplied from LDS.  Skinny products (few output tiles, long K) split K over
 // blocks; the slices go to a workspace and are added in a fixed order.
 // Accumulator element e of lane l is row 4e + l/16, column l%16 of its 16 x 16 tile.
@@ -38,6 +41,24 @@ RR_DEV void gm_load(const T* __restrict__ A, int64_t lda, int64_t rows, int64_t 
         v[s] = x;
     }
 }
+// The same where all of the step's k are in range: bytes from the tile's origin, the
+// same in every step (rows past the operand's end read its last row: what they give is
+// not stored), so a step's loads take a scalar base and no vector arithmetic.
+template <typename T, bool TR>
+RR_DEV void gm_offsets(int64_t lda, int64_t rows, int t, uint32_t (&o)[GM_EL]) {
+    const int last = (int)std::min<int64_t>(rows, GM_BM) - 1;
+#pragma unroll
+    for (int s = 0; s < GM_EL; ++s) {
+        const int i = std::min(TR ? (t >> 4) + 16 * s : t & 63, last);
+        const int k = TR ? t & 15 : (t >> 6) + 4 * s;
+        o[s] = (uint32_t)((TR ? k + i * lda : i + k * lda) * sizeof(T));
+    }
+}
+template <typename T>
+RR_DEV void gm_load_at(const T* __restrict__ base, const uint32_t (&o)[GM_EL], double (&v)[GM_EL]) {
+#pragma unroll
+    for (int s = 0; s < GM_EL; ++s) v[s] = (double)*(const T*)((const char*)base + o[s]);
+}
 template <bool TR>
 RR_DEV void gm_store(double (*S)[GM_BM + GM_PAD], int t, const double (&v)[GM_EL]) {
 #pragma unroll
@@ -50,7 +71,7 @@ RR_DEV void gm_store(double (*S)[GM_BM + GM_PAD], int t, const double (&v)[GM_EL
 }
 
 template <typename TA, typename TB, bool TRA, bool TRB, bool SYM = false>
-__global__ __launch_bounds__(GM_THREADS) void k_gemm_mfma(int64_t M, int64_t N, int64_t K,
+__global__ __launch_bounds__(GM_THREADS, 4) void k_gemm_mfma(int64_t M, int64_t N, int64_t K,
                                                           const TA* __restrict__ A, int64_t lda,
                                                           const TB* __restrict__ B, int64_t ldb,
                                                           double* __restrict__ C, int64_t ldc,
@@ -58,8 +79,8 @@ __global__ __launch_bounds__(GM_THREADS) void k_gemm_mfma(int64_t M, int64_t N, 
                                                           double* __restrict__ part, int64_t gn,
                                                           int64_t ntiles, int64_t nwork, int64_t per_xcd,
                                                           bool b_upper) {
-    __shared__ double As[GM_BK][GM_BM + GM_PAD];
-    __shared__ double Bs[GM_BK][GM_BN + GM_PAD];
+    __shared__ double As[2][GM_BK][GM_BM + GM_PAD];
+    __shared__ double Bs[2][GM_BK][GM_BN + GM_PAD];
     // XCD-aware order: workgroups go to the 8 XCDs round robin, so block b runs on
     // XCD b % 8; each XCD takes one contiguous range of (slice, tile) indices, and
     // tiles that share an A row slab (and, split over K, the same K slice) meet in
@@ -97,42 +118,58 @@ __global__ __launch_bounds__(GM_THREADS) void k_gemm_mfma(int64_t M, int64_t N, 
 
     // op(B)[k][j] is op(B^T)[j][k]: load it with the transposed flag.  Two register
     // sets alternate between k steps, so a tile is loaded two steps before it is
-    // stored to LDS (the load latency of a step alone is not covered).
+    // stored to LDS (the load latency of a step alone is not covered); two LDS buffers
+    // leave one barrier a step.
+    uint32_t oa[GM_EL], ob[GM_EL];
+    gm_offsets<TA, TRA>(lda, M - i0, t, oa);
+    gm_offsets<TB, !TRB>(ldb, N - j0, t, ob);
+    const TA* Ab = A + (TRA ? i0 * lda : i0);
+    const TB* Bb = B + (TRB ? j0 : j0 * ldb);
+    const int64_t sa = TRA ? 1 : lda, sb = TRB ? ldb : 1;   // to the next k
     double ra0[GM_EL], rb0[GM_EL], ra1[GM_EL], rb1[GM_EL];
-    if (kb < ke) {
-        gm_load<TA, TRA>(A, lda, M, ke, i0, kb, t, ra0);
-        gm_load<TB, !TRB>(B, ldb, N, ke, j0, kb, t, rb0);
-    }
-    if (kb + GM_BK < ke) {
-        gm_load<TA, TRA>(A, lda, M, ke, i0, kb + GM_BK, t, ra1);
-        gm_load<TB, !TRB>(B, ldb, N, ke, j0, kb + GM_BK, t, rb1);
-    }
-    auto step = [&](int64_t k0, double (&ra)[GM_EL], double (&rb)[GM_EL]) {
-        gm_store<TRA>(As, t, ra);
-        gm_store<!TRB>(Bs, t, rb);
-        __syncthreads();
-        if (k0 + 2 * GM_BK < ke) {
-            gm_load<TA, TRA>(A, lda, M, ke, i0, k0 + 2 * GM_BK, t, ra);
-            gm_load<TB, !TRB>(B, ldb, N, ke, j0, k0 + 2 * GM_BK, t, rb);
-        }
+    // whole steps (none where a byte offset within a tile would not fit 32 bits)
+    const bool wide = std::max<int64_t>((TRA ? GM_BM : GM_BK) * lda, (TRB ? GM_BK : GM_BN) * ldb) >= (int64_t)1 << 28;
+    const int64_t kf = kb + (ke > kb && !wide ? (ke - kb) / GM_BK * GM_BK : 0);
+    auto load = [&](int64_t k0, double (&ra)[GM_EL], double (&rb)[GM_EL]) {
+        gm_load_at(Ab + k0 * sa, oa, ra);
+        gm_load_at(Bb + k0 * sb, ob, rb);
+    };
+    if (kb < kf) load(kb, ra0, rb0);
+    if (kb + GM_BK < kf) load(kb + GM_BK, ra1, rb1);
+    auto multiply = [&](int buf) {
 #pragma unroll
         for (int kc = 0; kc < GM_BK; kc += 4) {
             double a[2], b[2];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) a[u] = As[kc + (lane >> 4)][wm * 32 + u * 16 + (lane & 15)];
+            for (int u = 0; u < 2; ++u) a[u] = As[buf][kc + (lane >> 4)][wm * 32 + u * 16 + (lane & 15)];
 #pragma unroll
-            for (int v = 0; v < 2; ++v) b[v] = Bs[kc + (lane >> 4)][wn * 32 + v * 16 + (lane & 15)];
+            for (int v = 0; v < 2; ++v) b[v] = Bs[buf][kc + (lane >> 4)][wn * 32 + v * 16 + (lane & 15)];
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
                 for (int v = 0; v < 2; ++v)
                     acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
         }
-        __syncthreads();
     };
-    for (int64_t k0 = kb; k0 < ke; k0 += 2 * GM_BK) {
-        step(k0, ra0, rb0);
-        if (k0 + GM_BK < ke) step(k0 + GM_BK, ra1, rb1);
+    auto step = [&](int64_t k0, int buf, double (&ra)[GM_EL], double (&rb)[GM_EL]) {
+        gm_store<TRA>(As[buf], t, ra);
+        gm_store<!TRB>(Bs[buf], t, rb);
+        __syncthreads();
+        if (k0 + 2 * GM_BK < kf) load(k0 + 2 * GM_BK, ra, rb);
+        multiply(buf);
+    };
+    for (int64_t k0 = kb; k0 < kf; k0 += 2 * GM_BK) {
+        step(k0, 0, ra0, rb0);
+        if (k0 + GM_BK < kf) step(k0 + GM_BK, 1, ra1, rb1);
+    }
+    for (int64_t k0 = kf; k0 < ke; k0 += GM_BK) {   // the last k, short of a step: zeros past ke
+        gm_load<TA, TRA>(A, lda, M, ke, i0, k0, t, ra0);
+        gm_load<TB, !TRB>(B, ldb, N, ke, j0, k0, t, rb0);
+        __syncthreads();
+        gm_store<TRA>(As[0], t, ra0);
+        gm_store<!TRB>(Bs[0], t, rb0);
+        __syncthreads();
+        multiply(0);
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {

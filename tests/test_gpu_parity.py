@@ -397,6 +397,21 @@ def test_build_fp64_wide_triangular_inverse(n, l):
     test_build_fp64_triangular_inverse_widths(n, l)
 
 
+@pytest.mark.parametrize("rows,k", [(3001, 33), (3001, 48), (2048, 65), (4099, 130)])
+def test_gemm_edges_through_orthonormal_basis(rows, k):
+    """Products whose tiles end inside a row block, a column block and a k step: an
+    orthonormalised block and its triangular factor."""
+    prob = workloads.cfg_small_dense(n=rows, d=8, l=k)
+    kop = rr.kernel_operator(rr.OP_RBF, _cuda(prob.pts), prob.kconst, prob.scale)
+    A = rr.kernel_to_dense(kop, "fp64")
+    P = rr.build_precond(rr.dense_operator(A), [prob.mus[0]], l=k, sketch="gaussian", seed=rows)
+    g = P.export(0)
+    Om = _cuda(orng.gaussian_matrix(rows, rows, k))
+    Y = (A @ Om + prob.mus[0] * Om).cpu().numpy()
+    assert np.abs(g["Q"].T @ g["Q"] - np.eye(k)).max() < 1e-12
+    assert np.linalg.norm(g["Q"] @ g["R"] - Y) < 1e-12 * np.linalg.norm(Y)
+
+
 @pytest.mark.parametrize("l", [0, 45])
 @pytest.mark.parametrize("use_graph", [False, True])
 def test_solve_fp64_matches_oracle(dense_small, l, use_graph):
