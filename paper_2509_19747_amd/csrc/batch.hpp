@@ -179,7 +179,9 @@ struct Batch {
         }
         if (is_kernel(P.op)) {
             const KernelOp k = kernel_op_of(P);
-            if (fp64 || P.opts.prec == RR_PREC_FP64) launch_kernel_matmat_f64(k, muc, Pin, ldp, mc, Wout, n, st);
+            if (fp64 || P.opts.prec == RR_PREC_FP64) 
+                launch_kernel_matmat_f64(k, muc, Pin, ldp, mc, Wout, n, kws.as<double>(),
+                                         kmulti ? 0 : kws.bytes() / sizeof(double), st);
             else launch_kernel_matmat_bf16x6(k, muc, Pin, ldp, mc, Wout, n, kws.ptr(), kws.bytes(), st);
         } else {
             if (!fp64 && P.A32.ptr()) gemm(false, false, n, mc, n, P.A32.ptr(), P.lda32, Pin, ldp, Wout, n, 1.0, 0.0, DT_F32);

@@ -298,9 +298,10 @@ void launch_dense_gemm_bf16(int64_t n, int64_t m, const void* A, int64_t lda, co
                             int64_t ldb, double mu, float* Y, int64_t ldy, hipStream_t st);
 
 // ------------------------------------------------------------ batched solve
-// W = scale*K P + diag(mucol) P for m columns on float64 MFMA with float64 entries.
+// W = scale*K P + diag(mucol) P for m columns on float64 MFMA with float64 entries; ws (may
+// be empty): partial sums of as many splits of the points as it holds.
 void launch_kernel_matmat_f64(const KernelOp& op, const double* mucol, const double* P, int64_t ldp, int64_t m,
-                              double* W, int64_t ldw, hipStream_t st);
+                              double* W, int64_t ldw, double* ws, size_t ws_doubles, hipStream_t st);
 // The same in the working precision (kernels_kgemm.hip): float32-class entries times P in
 // float32 by exact bf16 pieces; needs op.rrec and op.crec; ws: kernel_matmat_ws_bytes for n
 // and at least m columns.

@@ -15,23 +15,28 @@
 namespace rr {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
-constexpr int KD_BM = 128, KD_BN = 128, KD_BK = 16, KD_THREADS = 512;
+constexpr int KD_BM = 128, KD_BK = 16, KD_THREADS = 512;
+constexpr int KD_CUS = 256, KD_SPLITS = 16;
 
-// Block: 8 waves in a 2 (rows) x 4 (columns) grid of 64 x 32 wave tiles (4 x 2 MFMA
-// tiles, 32 float64 accumulators per lane), two blocks per compute unit: the float64
-// MFMA pipe needs several resident waves to stay busy, and one block forms entries while
-// the other multiplies (n = 20,000, 256 columns: 6.6 ms; one block of 256 rows a compute
-// unit left 98 units idle and took 17.2).  Per step of 16 points the
-// block forms the 128 x 16 kernel tile (thread: one row, 4 points whose records
+// Block: 8 waves in a 2 (rows) x 4 (columns) grid of 64 x 16 NV wave tiles (4 x NV MFMA
+// tiles, 16 NV float64 accumulators per lane), one block a compute unit.  Per step of 16
+// points the block forms the 128 x 16 kernel tile (thread: one row, 4 points whose records
 // arrive through scalar loads; float64 entries: difference form, float64 exp) into
-// LDS (k-major) and stages the 16 x 128 slice of P.
-template <int KIND, int DM>
+// LDS (k-major) and stages the 16 x 64 NV slice of P.
+// The vector ALU does not run beside the float64 MFMA: a step of a wave is about 1100
+// cycles of entries and 1024 NV of MFMA, so the wide block (NV = 4, 256 columns) forms
+// each entry once where two of 128 would twice.  The points are split over blockIdx.z
+// (part: float64 partial sums, added in order by k_kgemm_f64_finish) so that the blocks
+// come in full rounds of the 256 compute units.  n = 20,000, d = 16, 256 columns: 4.4 ms
+// (128 columns a block, no splits, whose 314 blocks take two rounds: 6.6).
+template <int KIND, int DM, int NV>
 __global__ __launch_bounds__(KD_THREADS) void k_kgemm_f64_mfma(
     int64_t n, const float* __restrict__ xa, double g, double kconst, double scale,
     const double* __restrict__ mucol, const double* __restrict__ P, int64_t ldp, int64_t m,
-    double* __restrict__ W, int64_t ldw) {
+    double* __restrict__ W, int64_t ldw, int64_t points, double* __restrict__ part) {
+    constexpr int BN = 64 * NV, NP = BN * KD_BK / KD_THREADS;
     __shared__ double As[KD_BK][KD_BM + 2];
-    __shared__ double Bs[KD_BK][KD_BN + 2];
+    __shared__ double Bs[KD_BK][BN + 2];
     __shared__ double tab[EXP2_TAB];
     exp2_table_fill(tab);
     __syncthreads();
@@ -39,7 +44,8 @@ __global__ __launch_bounds__(KD_THREADS) void k_kgemm_f64_mfma(
     const int lane = t & 63, wave = t >> 6;
     const int wm = wave & 1, wn = wave >> 1;
     const int64_t i0 = (int64_t)blockIdx.x * KD_BM;
-    const int64_t c0 = (int64_t)blockIdx.y * KD_BN;
+    const int64_t c0 = (int64_t)blockIdx.y * BN;
+    const int64_t jb = blockIdx.z * points, je = std::min(n, jb + points);
 
     const int trow = t & (KD_BM - 1);
     const int pg = __builtin_amdgcn_readfirstlane(t / KD_BM);   // 0..3: which 4 of the 16 points
@@ -48,16 +54,16 @@ __global__ __launch_bounds__(KD_THREADS) void k_kgemm_f64_mfma(
     float xi[DM];
 #pragma unroll
     for (int k = 0; k < DM; ++k) xi[k] = xa[gic * DM + k];
-    f64x4 acc[4][2];
+    f64x4 acc[4][NV];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int v = 0; v < 2; ++v) acc[u][v] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int v = 0; v < NV; ++v) acc[u][v] = f64x4{0.0, 0.0, 0.0, 0.0};
 
     // the next step's point records (wave-uniform) and P values are loaded while the
     // current step's MFMAs run
     float xj[4][DM];
-    double pv[4];
+    double pv[NP];
     auto load = [&](int64_t j0) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -67,13 +73,13 @@ __global__ __launch_bounds__(KD_THREADS) void k_kgemm_f64_mfma(
             for (int k = 0; k < DM; ++k) xj[e][k] = xa[gjc * DM + k];
         }
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < NP; ++s) {
             const int64_t gj = j0 + (t & 15), gc = c0 + (t >> 4) + 32 * s;
             pv[s] = (gj < n && gc < m) ? P[gj + gc * ldp] : 0.0;
         }
     };
-    load(0);
-    for (int64_t j0 = 0; j0 < n; j0 += KD_BK) {
+    if (jb < je) load(jb);
+    for (int64_t j0 = jb; j0 < je; j0 += KD_BK) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int p = pg * 4 + e;
@@ -87,20 +93,20 @@ __global__ __launch_bounds__(KD_THREADS) void k_kgemm_f64_mfma(
             As[p][trow] = (j0 + p < n) ? kentry64<KIND>(-0.5 * g * r2, kconst, tab) : 0.0;
         }
 #pragma unroll
-        for (int s = 0; s < 4; ++s) Bs[t & 15][(t >> 4) + 32 * s] = pv[s];
-        if (j0 + KD_BK < n) load(j0 + KD_BK);
+        for (int s = 0; s < NP; ++s) Bs[t & 15][(t >> 4) + 32 * s] = pv[s];
+        if (j0 + KD_BK < je) load(j0 + KD_BK);
         __syncthreads();
 #pragma unroll
         for (int kc = 0; kc < KD_BK; kc += 4) {
-            double a[4], b[2];
+            double a[4], b[NV];
 #pragma unroll
             for (int u = 0; u < 4; ++u) a[u] = As[kc + (lane >> 4)][wm * 64 + u * 16 + (lane & 15)];
 #pragma unroll
-            for (int v = 0; v < 2; ++v) b[v] = Bs[kc + (lane >> 4)][wn * 32 + v * 16 + (lane & 15)];
+            for (int v = 0; v < NV; ++v) b[v] = Bs[kc + (lane >> 4)][(wn * NV + v) * 16 + (lane & 15)];
 #pragma unroll
             for (int u = 0; u < 4; ++u)
 #pragma unroll
-                for (int v = 0; v < 2; ++v)
+                for (int v = 0; v < NV; ++v)
                     acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
         }
         __syncthreads();
@@ -108,8 +114,8 @@ __global__ __launch_bounds__(KD_THREADS) void k_kgemm_f64_mfma(
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
 #pragma unroll
-        for (int v = 0; v < 2; ++v) {
-            const int64_t gc = c0 + wn * 32 + v * 16 + (lane & 15);
+        for (int v = 0; v < NV; ++v) {
+            const int64_t gc = c0 + (wn * NV + v) * 16 + (lane & 15);
             if (gc >= m) continue;
             const double mu = mucol[gc];
             // v_mfma_f64_16x16x4_f64 result layout: element e of lane l is row 4*e + l/16,
@@ -117,31 +123,89 @@ __global__ __launch_bounds__(KD_THREADS) void k_kgemm_f64_mfma(
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int64_t gr = i0 + wm * 64 + u * 16 + 4 * e + (lane >> 4);
-                if (gr < n) W[gr + gc * ldw] = fma(scale, acc[u][v][e], mu * P[gr + gc * ldp]);
+                if (gr >= n) continue;
+                if (part) part[((int64_t)blockIdx.z * m + gc) * n + gr] = acc[u][v][e];
+                else W[gr + gc * ldw] = fma(scale, acc[u][v][e], mu * P[gr + gc * ldp]);
             }
         }
     }
 }
 
-template <int KIND>
-static void kd_dispatch(const KernelOp& op, const double* mucol, const double* P, int64_t ldp, int64_t m, double* W,
-                        int64_t ldw, hipStream_t st) {
-    dim3 grid((unsigned)((op.n + KD_BM - 1) / KD_BM), (unsigned)((m + KD_BN - 1) / KD_BN));
+__global__ __launch_bounds__(256) void k_kgemm_f64_finish(int64_t n, int64_t m, int splits,
+                                                          const double* __restrict__ part, double scale,
+                                                          const double* __restrict__ mucol,
+                                                          const double* __restrict__ P, int64_t ldp,
+                                                          double* __restrict__ W, int64_t ldw) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, j = blockIdx.y;
+    if (i >= n) return;
+    double v[KD_SPLITS], s = 0.0;
+#pragma unroll
+    for (int z = 0; z < KD_SPLITS; ++z) v[z] = z < splits ? part[((int64_t)z * m + j) * n + i] : 0.0;
+#pragma unroll
+    for (int z = 0; z < KD_SPLITS; ++z) s += v[z];
+    W[i + j * ldw] = fma(scale, s, mucol[j] * P[i + j * ldp]);
+}
+
+// The block width by the cheaper sum over the column blocks (a step costs 1.07 entries to
+// 1 NV of MFMA), and the splits (of 256 points at least, as far as max_part doubles of
+// partials go) whose last round of blocks is fullest, a split more for 1 % of it at least.
+struct KdPlan {
+    int nv, splits;
+    int64_t cbs, points;
+};
+static KdPlan kd_plan(int64_t n, int64_t m, int dm, size_t max_part) {
+    KdPlan p;
+    const int64_t c2 = (m + 127) / 128, c4 = (m + 255) / 256;
+    p.nv = dm <= 16 && c4 * (107 + 400) < c2 * (107 + 200) ? 4 : 2;   // (dm = 32 would spill)
+    p.cbs = p.nv == 4 ? c4 : c2;
+    const int64_t units = (n + KD_BM - 1) / KD_BM * p.cbs, steps = (n + KD_BK - 1) / KD_BK;
+    p.splits = 1;
+    double best = 0.0;
+    for (int s = 1; s <= KD_SPLITS; ++s) {
+        if (s > 1 && ((size_t)s * m * n > max_part || steps / s < 16)) break;
+        const int64_t blocks = units * s, rounds = (blocks + KD_CUS - 1) / KD_CUS;
+        const double full = (double)blocks / (double)(rounds * KD_CUS) - 0.01 * s;
+        if (full > best) {
+            best = full;
+            p.splits = s;
+        }
+    }
+    p.points = (steps + p.splits - 1) / p.splits * KD_BK;
+    p.splits = (int)((n + p.points - 1) / p.points);
+    return p;
+}
+
+template <int KIND, int NV>
+static void kd_dispatch(const KernelOp& op, const KdPlan& p, const double* mucol, const double* P, int64_t ldp, int64_t m,
+                        double* W, int64_t ldw, double* part, hipStream_t st) {
+    dim3 grid((unsigned)((op.n + KD_BM - 1) / KD_BM), (unsigned)p.cbs, (unsigned)p.splits);
     const double g = kernel_g64(op.kind, op.kconst);
-#define KDL(DD) k_kgemm_f64_mfma<KIND, DD><<<grid, KD_THREADS, 0, st>>>(op.n, op.xa, g, op.kconst, op.scale, mucol, P, ldp, m, W, ldw)
+#define KDL(DD) k_kgemm_f64_mfma<KIND, DD, NV><<<grid, KD_THREADS, 0, st>>>(op.n, op.xa, g, op.kconst, op.scale, mucol, P, ldp, m, W, ldw, p.points, part)
     switch (op.dm) {
         case 4: KDL(4); break;
         case 8: KDL(8); break;
         case 16: KDL(16); break;
-        default: KDL(32); break;
+        default:
+            if constexpr (NV == 2) KDL(32);
+            break;
     }
 #undef KDL
 }
 
 void launch_kernel_matmat_f64(const KernelOp& op, const double* mucol, const double* P, int64_t ldp, int64_t m,
-                              double* W, int64_t ldw, hipStream_t st) {
-    if (op.kind == 1) kd_dispatch<1>(op, mucol, P, ldp, m, W, ldw, st);
-    else kd_dispatch<2>(op, mucol, P, ldp, m, W, ldw, st);
+                              double* W, int64_t ldw, double* ws, size_t ws_doubles, hipStream_t st) {
+    const KdPlan p = kd_plan(op.n, m, op.dm, ws_doubles);
+    double* part = p.splits > 1 ? ws : nullptr;
+    if (op.kind == 1) {
+        if (p.nv == 4) kd_dispatch<1, 4>(op, p, mucol, P, ldp, m, W, ldw, part, st);
+        else kd_dispatch<1, 2>(op, p, mucol, P, ldp, m, W, ldw, part, st);
+    } else {
+        if (p.nv == 4) kd_dispatch<2, 4>(op, p, mucol, P, ldp, m, W, ldw, part, st);
+        else kd_dispatch<2, 2>(op, p, mucol, P, ldp, m, W, ldw, part, st);
+    }
+    if (part)
+        k_kgemm_f64_finish<<<dim3((unsigned)((op.n + 255) / 256), (unsigned)m), 256, 0, st>>>(
+            op.n, m, p.splits, part, op.scale, mucol, P, ldp, W, ldw);
 }
 
 // W[:, j] += mu_j P[:, j] for a dense operator product computed by the GEMM.

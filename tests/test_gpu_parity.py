@@ -776,6 +776,32 @@ def test_wide_kernel_product(kind, n, d, m):
         assert infos[j]["relres_work"] <= 1e-4
 
 
+@pytest.mark.parametrize("kind,n,d,m,prec", [(rr.OP_RBF, 700, 3, 129, "fp32"), (rr.OP_MATERN32, 1500, 16, 256, "fp32"),
+                                             (rr.OP_RBF, 1500, 8, 300, "fp64"), (rr.OP_RBF, 1031, 20, 257, "fp32"),
+                                             (rr.OP_RBF, 4100, 16, 40, "fp32"), (rr.OP_MATERN32, 300, 4, 600, "fp64")])
+def test_wide_kernel_product_float64(kind, n, d, m, prec):
+    """The float64 product of many columns (both block widths, the points split and whole,
+    ragged rows, columns and last split): the final residuals, which come from it, against
+    those of the same X formed by the oracle's operator."""
+    rng = np.random.default_rng(n + m)
+    pts = rng.standard_normal((d, n)).astype(np.float32)
+    mu = 1e-2
+    op = Operator(kind=kind, pts=pts, kconst=0.5 / d, scale=1.0 / n)
+    B = rng.standard_normal((n, m))
+    kop = rr.kernel_operator(kind, _cuda(pts), 0.5 / d, 1.0 / n)
+    P = rr.build_precond(kop, [mu], l=20, sketch="gaussian", seed=5, prec=prec)
+    X, infos, st = P.solve_batch(_cuda(B), [0] * m, tol=1e-7)
+    X = X.cpu().numpy()
+    assert st == rr.RR_OK
+    R = B - (op.matmat(X) + mu * X)
+    # sums of n terms to n + 60 roundings (entry and sums) on either side
+    E = 2.0 * (n + 60) * 2.0**-53 * (op.matmat(np.abs(X)) + mu * np.abs(X) + np.abs(B))
+    for j in range(m):
+        nb = np.linalg.norm(B[:, j])
+        assert abs(infos[j]["relres_fp64"] - np.linalg.norm(R[:, j]) / nb) <= np.linalg.norm(E[:, j]) / nb, j
+        assert infos[j]["relres_fp64"] <= 1e-7
+
+
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 def test_batched_multi_shift_matches_single_and_oracle(prec):
     # every RHS under every shift (joint basis), one fused batched solve, compared with
