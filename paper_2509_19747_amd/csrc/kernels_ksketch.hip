@@ -9,8 +9,8 @@
 // column tile, so every kernel entry is formed once per row tile); wave w owns
 // rows 64*(w&1)..+63 and columns 128*((w>>1)&3)..+127 (2 x 4 MFMA tiles of
 // 32 x 32).  Per step of 32 points the block forms the 128 x 32 kernel tile and
-// stages the 32 x 512 slice of Omega in LDS (thread t: column t, loaded into
-// registers up to three steps ahead).  The kernel tile is formed on the matrix cores too:
+// stages the 32 x 512 slice of Omega in LDS (loaded into registers up to three
+// steps ahead).  The kernel tile is formed on the matrix cores too:
 // waves 0-3 each form one 32 x 32 quarter as the product of augmented point
 // records (kmma.hpp: float32-class exponents from three-piece bf16 splits), then
 // exp2 and the hi/lo split on the vector ALU.  The records of the block's rows
@@ -50,20 +50,26 @@ struct Ks2Smem {
     uint16_t b[2][KS2_BN * KS2_BS];
 };
 
-// Omega slice of one step: thread t owns column c0 + t and its 32 points, as
-// four 16-byte chunks (global loads into registers ahead of use; the LDS
-// store of consecutive columns hits distinct banks).  B's rows [n, round8(n))
-// are zero, so a chunk is either inside the padded column or wholly past it.
-RR_DEV void ks2_load_b(const uint16_t* src, int64_t npad, int64_t k0, int cb, uint4 (&rb)[KS2_CPT]) {
+// Omega slice of one step: 512 columns of 32 points, as four 16-byte chunks each (global
+// loads into registers ahead of use).  Thread t takes chunk t % 4 of columns t / 4 + 128 s:
+// a load touches 64 contiguous bytes of 16 columns, and its LDS store 128 distinct bytes of
+// banks per eight lanes (with a thread per column, four chunks of it, each load touched 64
+// lines, as long to serve as the step's MFMAs: n = 32,768, 1,024 columns 6.2, so 5.2
+// ms).  B's rows [n, round8(n)) are zero, so a chunk is either inside the padded
+// column or wholly past it; columns past the last are zeros.
+// src: the first column of the wave (wave-uniform: a scalar base and one 32-bit offset keep
+// the addresses out of the registers), cols: the columns from the thread's first one on.
+RR_DEV void ks2_load_b(const uint16_t* src, int64_t ldb, uint32_t off, int cols, int64_t npad, int64_t k0, int q,
+                       uint4 (&rb)[KS2_CPT]) {
 #pragma unroll
     for (int s = 0; s < KS2_CPT; ++s) {
-        const int64_t gj = k0 + 8 * (cb + s);
-        rb[s] = (src && gj < npad) ? *(const uint4*)(src + gj) : make_uint4(0u, 0u, 0u, 0u);
+        const char* base = (const char*)(src + KS2_THREADS / 4 * s * ldb + k0);
+        rb[s] = KS2_THREADS / 4 * s < cols && k0 + 8 * q < npad ? *(const uint4*)(base + off) : make_uint4(0u, 0u, 0u, 0u);
     }
 }
-RR_DEV void ks2_store_b(Ks2Smem& sm, int buf, int col, int cb, const uint4 (&rb)[KS2_CPT]) {
+RR_DEV void ks2_store_b(Ks2Smem& sm, int buf, int col, int q, const uint4 (&rb)[KS2_CPT]) {
 #pragma unroll
-    for (int s = 0; s < KS2_CPT; ++s) *(uint4*)&sm.b[buf][col * KS2_BS + 8 * (cb + s)] = rb[s];
+    for (int s = 0; s < KS2_CPT; ++s) *(uint4*)&sm.b[buf][(col + KS2_THREADS / 4 * s) * KS2_BS + 8 * q] = rb[s];
 }
 
 // One step of MFMAs for the wave's 64 x (32 KS2_WC) tile, in two half steps of 16
@@ -209,9 +215,11 @@ __global__ __launch_bounds__(KS2_THREADS) void k_ksketch_bf16x2(
 #pragma unroll
             for (int j = 0; j < 16; ++j) acc[u][v][j] = 0.0f;
 
-    // Omega staging: thread t owns chunks cb .. cb + KS2_CPT - 1 of column bcol
-    const int bcol = t / (4 / KS2_CPT), bcb = (t % (4 / KS2_CPT)) * KS2_CPT;
-    const uint16_t* bsrc = (c0 + bcol < m) ? Bm + (c0 + bcol) * ldb : nullptr;
+    // Omega staging: thread t owns chunk bq of columns bcol + 128 s
+    const int bcol = t >> 2, bq = t & 3;
+    const uint16_t* bsrc = Bm + (c0 + 16 * __builtin_amdgcn_readfirstlane(wave)) * ldb;
+    const uint32_t boff = (uint32_t)((lane >> 2) * ldb + 8 * bq) * 2;
+    const int bcols = (int)(m - c0 - bcol < KS2_BN ? m - c0 - bcol : KS2_BN);
     const int64_t npad = (n + 7) & ~(int64_t)7;   // B rows [n, npad) hold zeros
     if constexpr (GEN) {
         // sign table: entry e = the 8 bf16 values (-1 where bit t of e is set, else +1)
@@ -256,11 +264,11 @@ __global__ __launch_bounds__(KS2_THREADS) void k_ksketch_bf16x2(
     uint4 rx[KS2_CPT], ry[KS2_CPT];
     __syncthreads();   // row records
     if (kb < ke) {
-        ks2_load_b(bsrc, npad, kb, bcb, rx);
-        ks2_store_b(sm, 0, bcol, bcb, rx);
+        ks2_load_b(bsrc, ldb, boff, bcols, npad, kb, bq, rx);
+        ks2_store_b(sm, 0, bcol, bq, rx);
         if (former) form(kb, 0);
-        ks2_load_b(bsrc, npad, kb + KS2_BK, bcb, rx);
-        ks2_load_b(bsrc, npad, kb + 2 * KS2_BK, bcb, ry);
+        ks2_load_b(bsrc, ldb, boff, bcols, npad, kb + KS2_BK, bq, rx);
+        ks2_load_b(bsrc, ldb, boff, bcols, npad, kb + 2 * KS2_BK, bq, ry);
     }
     __syncthreads();
     int buf = 0;
@@ -268,8 +276,8 @@ __global__ __launch_bounds__(KS2_THREADS) void k_ksketch_bf16x2(
     auto step = [&](int64_t kc, uint4 (&rb)[KS2_CPT]) {
         const int64_t k1 = kc + KS2_BK;
         if (k1 < ke) {
-            ks2_store_b(sm, buf ^ 1, bcol, bcb, rb);
-            ks2_load_b(bsrc, npad, kc + 3 * KS2_BK, bcb, rb);
+            ks2_store_b(sm, buf ^ 1, bcol, bq, rb);
+            ks2_load_b(bsrc, ldb, boff, bcols, npad, kc + 3 * KS2_BK, bq, rb);
         }
         // the forming wave of each SIMD builds the next tile while its partner's
         // product MFMAs run, then issues its own
