@@ -57,6 +57,7 @@ struct StreamCache {
     hipStream_t st;
     std::vector<CachedBlock> blocks;   // oldest first
     size_t total = 0;
+    bool pooled = false;               // of a stream of the library's own (trim_stream_blocks)
 };
 constexpr size_t kStreamCacheCap = (size_t)4 << 30;
 std::mutex g_cache_mu;
@@ -66,7 +67,7 @@ std::vector<CachedBlock> g_live;   // blocks handed out by Alloc::get (pointer, 
 StreamCache& cache_for(int dev, hipStream_t st) {
     for (auto& c : g_caches)
         if (c.dev == dev && c.st == st) return c;
-    g_caches.push_back(StreamCache{dev, st, {}, 0});
+    g_caches.push_back(StreamCache{dev, st, {}, 0, false});
     return g_caches.back();
 }
 
@@ -131,17 +132,31 @@ void* Alloc::get(size_t bytes) const {
     return p;
 }
 
-void release_stream_blocks(hipStream_t st) {
+void trim_stream_blocks(hipStream_t st, size_t share, size_t bound) {
     int dev = 0;
     (void)hipGetDevice(&dev);
     std::lock_guard<std::mutex> lk(g_cache_mu);
-    for (size_t i = 0; i < g_caches.size(); ++i) {
-        StreamCache& c = g_caches[i];
-        if (c.dev != dev || c.st != st) continue;
-        for (auto& b : c.blocks) (void)hipFreeAsync(b.p, st);
-        g_caches.erase(g_caches.begin() + (std::ptrdiff_t)i);
-        return;
+    StreamCache* own = nullptr;
+    size_t others = 0;
+    for (StreamCache& c : g_caches) {
+        if (c.dev != dev) continue;
+        if (c.st == st) own = &c;
+        else if (c.pooled) others += c.total;
     }
+    if (!own) return;
+    own->pooled = true;
+    const size_t keep = std::min(share, bound > others ? bound - others : 0);
+    size_t drop = 0;
+    while (own->total > keep) {
+        (void)hipFreeAsync(own->blocks[drop].p, st);
+        own->total -= own->blocks[drop++].bytes;
+    }
+    own->blocks.erase(own->blocks.begin(), own->blocks.begin() + (std::ptrdiff_t)drop);
+}
+
+void release_cached_blocks() {
+    std::lock_guard<std::mutex> lk(g_cache_mu);
+    flush_all_caches();
 }
 
 namespace {

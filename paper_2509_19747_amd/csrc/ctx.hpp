@@ -51,11 +51,13 @@ rr_status guarded(F&& body) {
     }
 }
 
-// Device allocator: the caller's rr_allocator if given, else hipMalloc/hipFree.
-// Frees the blocks the allocator cache holds for stream st (on this device) and
-// forgets the stream: called before the library destroys a stream it created.
-void release_stream_blocks(hipStream_t st);
+// Frees the blocks the allocator cache holds for a pooled stream st (on this device), oldest
+// first, down to share bytes and to what all other such streams leave of bound.
+void trim_stream_blocks(hipStream_t st, size_t share, size_t bound);
+// Frees every cached block of streams that are not being captured.
+void release_cached_blocks();
 
+// Device allocator: the caller's rr_allocator if given, else hipMalloc/hipFree.
 struct Alloc {
     rr_allocator a{};
     bool custom = false;

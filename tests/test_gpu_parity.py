@@ -1013,6 +1013,32 @@ def test_serving_alone_equals_mixed_and_oracle():
             assert rel <= 1e-6 + dA * np.linalg.norm(mixed[i]["X"][:, j]) / np.linalg.norm(r["B"][:, j])
 
 
+@pytest.mark.parametrize("slots", [1, 3, 8])
+def test_serving_repeated_calls_on_kept_streams(slots):
+    """The workers' streams and blocks outlive a call: bursts of other sizes and slot counts
+    between, then the first burst again, bitwise as before, with a build and solve on the
+    caller's stream in between as alone."""
+    from paper_2509_19747_amd import binding as rb
+    kw = dict(graph_iters=8, build=dict(prec="fp32", sketch="gaussian"), solve=dict(tol=1e-6, certify=True))
+    reqs = [dict(r, t_arrival=0.0) for r in _serving_requests(6, 11)]
+    other = [dict(r, t_arrival=0.0) for r in _serving_requests(9, 12)]
+    first, st = rb.serve(reqs, max_slots=slots, **kw)
+    assert st["ok"] == len(reqs)
+    r = reqs[0]
+    kop = rr.kernel_operator(rr.OP_RBF, _cuda(r["pts"]), r["kconst"], r["scale"])
+    solve = lambda: rr.build_precond(kop, [r["mu"]], l=r["l"], sketch="gaussian", seed=3,
+                                     prec="fp32").solve(_cuda(r["B"][:, 0]), tol=1e-6)[0]
+    x = solve()
+    for s in (8, slots, 2):
+        _, st = rb.serve(other, max_slots=s, **kw)
+        assert st["ok"] == len(other)
+        assert torch.equal(solve(), x)
+        again, st = rb.serve(reqs, max_slots=slots, **kw)
+        assert st["ok"] == len(reqs)
+        for a, b in zip(first, again):
+            assert np.array_equal(a["X"], b["X"])
+
+
 def test_serving_stream_at_the_workload_sizes():
     """The first 24 requests of the serving workload's own stream (n log-uniform up to
     32,768, l = n/32, 1-8 right-hand sides, the bench's server settings): every request
