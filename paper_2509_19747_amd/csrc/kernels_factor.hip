@@ -25,16 +25,26 @@ constexpr int CH_NB = 32;
 // updates of both, all independent of one another, so a step's chain is a square root
 // and a division: 24.7 us a launch (with row k shared through LDS and the solve behind the
 // factorisation, each entry's sum a chain of its own: 30.3).
-// Block 0 writes R11 back (zeros below the diagonal) and raises the status word
-// when a pivot is not positive and finite.
+// R11 is written back (zeros below the diagonal) where no other block still reads A11: by
+// the only block, or, where several blocks share the row, by one more block of the next
+// launch, which factors prev again.  (Block 0 writing it at once could overtake a block
+// that starts late on a busy device.)  Block 0 raises the status word when a pivot is not
+// positive and finite.
 __global__ __launch_bounds__(64) void k_chol_panel(double* A, int64_t lda, int kb, int64_t rest,
-                                                   int32_t* status) {
+                                                   int32_t* status, double* prev) {
     if (*status) return;
     const int t = threadIdx.x;
+    const int panels = (int)gridDim.x - (prev ? 1 : 0);
+    const bool back = (int)blockIdx.x == panels;
+    double* D = back ? prev : A;
+    if (back) {
+        kb = CH_NB;
+        rest = 0;
+    }
     double col[CH_NB];
 #pragma unroll
     for (int i = 0; i < CH_NB; ++i)
-        col[i] = (t < kb && i <= t) ? A[i + (int64_t)t * lda] : 0.0;
+        col[i] = (t < kb && i <= t) ? D[i + (int64_t)t * lda] : 0.0;
     const int64_t jc = (int64_t)blockIdx.x * 64 + t;   // panel column of this thread
     double x[CH_NB];
 #pragma unroll
@@ -64,23 +74,23 @@ __global__ __launch_bounds__(64) void k_chol_panel(double* A, int64_t lda, int k
         for (int i = 0; i < CH_NB; ++i)
             if (i < kb) A[i + (kb + jc) * lda] = x[i];
     }
-    if (blockIdx.x == 0) {
-        if (t < kb)
+    if ((back || panels == 1) && t < kb)
 #pragma unroll
-            for (int i = 0; i < CH_NB; ++i)
-                if (i < kb) A[i + (int64_t)t * lda] = (i <= t) ? col[i] : 0.0;
-        if (t == 0 && bad) *status = 1;
-    }
+        for (int i = 0; i < CH_NB; ++i)
+            if (i < kb) D[i + (int64_t)t * lda] = (i <= t) ? col[i] : 0.0;
+    if (blockIdx.x == 0 && t == 0 && bad) *status = 1;
 }
 
 void launch_cholesky_upper(double* A, int64_t l, int64_t lda, int32_t* status, double* ws,
                            size_t ws_doubles, hipStream_t st) {
+    double* prev = nullptr;   // diagonal block whose factor is still to be written
     for (int64_t k0 = 0; k0 < l; k0 += CH_NB) {
         const int kb = (int)((l - k0 < CH_NB) ? l - k0 : CH_NB);
         double* A11 = A + k0 + k0 * lda;
         const int64_t rest = l - k0 - kb;
-        k_chol_panel<<<(unsigned)std::max<int64_t>((rest + 63) / 64, 1), 64, 0, st>>>(A11, lda, kb, rest,
-                                                                                     status);
+        const int64_t panels = std::max<int64_t>((rest + 63) / 64, 1);
+        k_chol_panel<<<(unsigned)(panels + (prev ? 1 : 0)), 64, 0, st>>>(A11, lda, kb, rest, status, prev);
+        prev = panels > 1 ? A11 : nullptr;
         if (rest > 0) {
             const double* A12 = A + k0 + (k0 + kb) * lda;
             double* A22 = A + (k0 + kb) + (k0 + kb) * lda;

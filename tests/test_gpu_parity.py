@@ -369,6 +369,28 @@ def test_cholesky_ladder_matches_oracle():
         rr.binding.cholesky_ladder(_cuda(W))
 
 
+@pytest.mark.parametrize("l", [97, 128, 230, 512])
+def test_cholesky_beside_other_work_is_bitwise_the_same(l):
+    """Factors of several blocks a block row, formed while another stream keeps the compute
+    units busy so that blocks of one launch start late, against the ones formed alone."""
+    g = torch.Generator(device="cuda").manual_seed(l)
+    M = torch.randn(l, 3 * l, device="cuda", dtype=torch.float64, generator=g)
+    W = M @ M.T / (3 * l)
+    R0, a0 = rr.binding.cholesky_ladder(W.clone())
+    assert a0 == 0.0
+    assert float((R0.T @ R0 - W).abs().max()) <= 1e-12 * l
+    B = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for _ in range(12):
+        with torch.cuda.stream(side):
+            for _ in range(6):
+                B @ B
+        R, a = rr.binding.cholesky_ladder(W.clone())
+        assert a == a0 and torch.equal(R, R0)
+    torch.cuda.synchronize()
+
+
 @pytest.mark.parametrize("n,l", [(300, 64), (320, 65), (600, 200), (800, 300)])
 def test_build_fp64_triangular_inverse_widths(n, l):
     """Basis widths at and across the row-slot sizes of the wave-per-column
