@@ -245,6 +245,10 @@ RR_DEV void lds_copy_32(const double* v, int t, int64_t n, int ntf, const double
     }
 }
 
+// Before a copy over LDS that this wave alone reads and has read in the same stage: the
+// compiler does not know of the copy, so nothing else keeps it behind those reads.
+RR_DEV void lds_reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
 // The lane number as a value that the compiler cannot see through: addresses formed from
 // it are formed where they are used instead of being held (and spilled) across a stage.
 RR_DEV int fresh_lane() {
@@ -287,10 +291,12 @@ RR_DEV void ksym_mma_item(int item, int64_t n, const bf16x8_t* __restrict__ rrec
     const uint32_t ur_off = (uint32_t)(size_t)(__attribute__((address_space(3))) double*)&urb[0][0];
     // records and u of the ts tiles from tile on, into the buffers' half kp; row >= 0:
     // also u of that row block, each wave its own 32 rows (urb is read when a row block
-    // begins, before the next one is fetched)
+    // begins; a block that starts with a row block's last stage reads it and fetches the
+    // next one's in the same stage)
     auto fetch = [&](int tile, int kp, int row) {
         const int lane = fresh_lane();
         if (row >= 0) {
+            lds_reads_done();
 #pragma unroll
             for (int p = 0; p < NR; ++p)
                 lds_copy_32(u + p * n, row * KM_CT + wave, n, ntf, zero, lane,
@@ -754,7 +760,8 @@ __global__ __launch_bounds__(KM_THREADS) __attribute__((amdgpu_waves_per_eu(NR =
                 }
         }
         if (ends) break;
-        if (wk.bi != bi) {   // this wave has read the last of its rows' h_i
+        if (wk.bi != bi) {   // this wave has read the last of its rows' h_i, and u if it formed no tile
+            lds_reads_done();
             const int t = wk.bi * KM_CT + wave, lane = fresh_lane();
 #pragma unroll
             for (int p = 0; p < NR; ++p) lds_copy_32(u + p * n, t, n, ntf, zero, lane, ur_off + (p * KM_RB + 32 * wave) * 8);

@@ -1745,3 +1745,26 @@ def test_edge_cases_of_the_variants():
                               basis=basis)
         xl, il = Pl.solve(_cuda(small.b), tol=1e-8, ok=(rr.RR_OK, rr.RR_ENOCONV), maxit=50)
         assert il["rc"] == rr.RR_OK and il["iters"] <= 2, (basis, il["iters"], il["tau"])
+
+
+@pytest.mark.parametrize("kind", [rr.OP_RBF, rr.OP_MATERN32])
+@pytest.mark.parametrize("n,d", [(2560, 4), (4096, 16), (5121, 8), (11_008, 20)])
+def test_kernel_matvec_blocks_from_a_last_range(kind, n, d):
+    """Sizes where blocks begin with the last column range of a row block, so that the rows'
+    u is read and the next row block's u fetched over it in one stage: one, two and four
+    columns in both precisions against the oracle's kernel formula, and equal in repeats."""
+    from oracle.operators import kernel_block
+    rng = np.random.default_rng(n + d)
+    pts = rng.standard_normal((d, n)).astype(np.float32)
+    kconst, scale, mu = 0.5 / d, 1.0 / n, 1e-3
+    U = rng.standard_normal((n, 4))
+    rows = np.unique(np.r_[np.arange(0, n, 61), n - 1])
+    ref = scale * (kernel_block(kind, kconst, pts.T[rows].astype(np.float64), pts.T.astype(np.float64)) @ U) + mu * U[rows]
+    kop = rr.kernel_operator(kind, _cuda(pts), kconst, scale)
+    for prec, tol in (("fp32", 2e-6), ("fp64", 1e-12)):
+        for cols in (1, 2, 4):
+            V = _cuda(U[:, :cols])
+            Y = rr.apply_operator_block(kop, mu, prec, V)
+            assert np.linalg.norm(Y.cpu().numpy()[rows] - ref[:, :cols]) <= tol * np.linalg.norm(ref[:, :cols]), (prec, cols)
+            for _ in range(5):
+                assert torch.equal(Y, rr.apply_operator_block(kop, mu, prec, V)), (prec, cols)
