@@ -613,7 +613,9 @@ RR_DEV void cg_rr_step(double rr, CgState* s) {
 }
 // Q^T r does not need that step's result: block 0 takes it while the others form the
 // product (a launch less in every iteration; once the step has stopped the cycle the
-// product is of no use and its partials are not read).
+// product is of no use and its partials are not read).  One thread reads the stop flag for
+// its block: block 0 may set it while others start, and the waves of a block have to agree
+// before gemv_t_block's barrier.
 __global__ __launch_bounds__(GT_THREADS) void k_gemv_t_rr(int64_t n, int64_t k, const double* __restrict__ Q,
                                                           int64_t ldq, const double* __restrict__ r,
                                                           double* __restrict__ c_part, int nchunks,
@@ -621,7 +623,10 @@ __global__ __launch_bounds__(GT_THREADS) void k_gemv_t_rr(int64_t n, int64_t k, 
                                                           int count, CgState* s) {
     static_assert(GT_THREADS == 256, "block_sum_array_1024");
     __shared__ double sc[16];
-    if (s->stop) return;
+    __shared__ int32_t stop;
+    if (threadIdx.x == 0) stop = s->stop;
+    __syncthreads();
+    if (stop) return;
     if (blockIdx.x == 0) {
         const double rr = block_sum_array_1024(part, count, sc);
         if (threadIdx.x == 0) cg_rr_step(rr, s);

@@ -1768,3 +1768,18 @@ def test_kernel_matvec_blocks_from_a_last_range(kind, n, d):
             assert np.linalg.norm(Y.cpu().numpy()[rows] - ref[:, :cols]) <= tol * np.linalg.norm(ref[:, :cols]), (prec, cols)
             for _ in range(5):
                 assert torch.equal(Y, rr.apply_operator_block(kop, mu, prec, V)), (prec, cols)
+
+
+def test_solve_stops_inside_a_batch_of_any_length():
+    """The stop test runs as a block of the projection's launch: wherever it falls in a batch
+    of launches, a solve gives the same bits, iterations and residuals."""
+    n, d = 9001, 8
+    rng = np.random.default_rng(3)
+    kop = rr.kernel_operator(rr.OP_RBF, _cuda(rng.standard_normal((d, n)).astype(np.float32)), 0.06, 1.0 / n)
+    P = rr.build_precond(kop, [1e-4], l=280, sketch="gaussian", seed=5, prec="fp32")
+    b = _cuda(rng.standard_normal(n))
+    x0, i0 = P.solve(b, tol=1e-8, check_every=1)
+    assert i0["rc"] == rr.RR_OK
+    for every in (2, 7, 64):
+        x, i = P.solve(b, tol=1e-8, check_every=every)
+        assert torch.equal(x, x0) and i["iters"] == i0["iters"] and i["relres_fp64"] == i0["relres_fp64"], every
