@@ -168,18 +168,25 @@ struct Batch {
             launch_add_shift_cols(n, mc, muc, Pin, ldp, Wout, n, st);
             return ColParts{nullptr, 0, 0, 0};
         }
-        if (kmulti && !fp64 && ldp == n) {
+        if (kmulti && !fp64) {
+            // (the workspace of few columns is the matvec's: never the wide product.  The
+            // caller's X may have longer columns: gathered into Z, which the next
+            // iteration recomputes before use)
+            if (ldp != n) {
+                launch_copy_cols(n, mc, nullptr, Pin, ldp, nullptr, Z.as<double>(), n, st);
+                Pin = Z.as<double>();
+            }
             const KernelOp k = kernel_op_of(P);
             const int nblk = kernel_matvec_blocks(n);
             launch_kernel_matvec_multi(k, false, Pin, (int)mc, single ? mu1 : 0.0, Wout, kdot.as<double>(),
                                        kws.as<double>(), nullptr, st);
             if (single) return ColParts{kdot.as<double>(), nblk, 1, nblk};
-            launch_add_shift_cols(n, mc, muc, Pin, ldp, Wout, n, st);
+            launch_add_shift_cols(n, mc, muc, Pin, n, Wout, n, st);
             return ColParts{nullptr, 0, 0, 0};
         }
         if (is_kernel(P.op)) {
             const KernelOp k = kernel_op_of(P);
-            if (fp64 || P.opts.prec == RR_PREC_FP64) 
+            if (fp64 || P.opts.prec == RR_PREC_FP64)
                 launch_kernel_matmat_f64(k, muc, Pin, ldp, mc, Wout, n, kws.as<double>(),
                                          kmulti ? 0 : kws.bytes() / sizeof(double), st);
             else launch_kernel_matmat_bf16x6(k, muc, Pin, ldp, mc, Wout, n, kws.ptr(), kws.bytes(), st);

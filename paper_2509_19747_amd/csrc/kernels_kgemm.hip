@@ -21,6 +21,7 @@
 // kernel took 4.47; n = 5,003, 100 columns: 67 against 500 us.  The relative error
 // against 64 bits is 1.4e-7 to 1.8e-7 over such sizes (1.6e-7 to 2.3e-7 before).
 #include "common.hpp"
+#include "ctx.hpp"
 #include "kentry.hpp"
 #include "kernels.hpp"
 #include "kmma.hpp"
@@ -282,6 +283,7 @@ void launch_kernel_matmat_bf16x6(const KernelOp& op, const double* mucol, const 
         // (a workspace made for more columns holds this chunk's packed P; its splits take
         // what is left)
         const size_t pkb = kg_plan(op.n, mc, 0).packed_bytes(mc);
+        RR_REQUIRE(ws_bytes >= pkb, "workspace too small for the wide kernel product");
         const KgPlan p = kg_plan(op.n, mc, std::min(KG_PART_MAX, (ws_bytes - pkb) / sizeof(double)));
         bf16x8_t* pk = (bf16x8_t*)ws;
         double* part = p.splits > 1 ? (double*)((char*)ws + pkb) : nullptr;

@@ -1783,3 +1783,38 @@ def test_solve_stops_inside_a_batch_of_any_length():
     for every in (2, 7, 64):
         x, i = P.solve(b, tol=1e-8, check_every=every)
         assert torch.equal(x, x0) and i["iters"] == i0["iters"] and i["relres_fp64"] == i0["relres_fp64"], every
+
+
+@pytest.mark.parametrize("n,d,nrhs", [(1000, 4, 1), (1000, 4, 2), (1023, 20, 2), (2047, 17, 1), (2816, 32, 3)])
+def test_solve_batch_few_columns_with_longer_columns_of_x(n, d, nrhs):
+    """Few columns without refinement, X with a leading dimension above n and a start of its
+    own (its first residual is a product with all of X's columns): the bits of the solve
+    with ldx = n, the rows between the columns untouched, and the residual within the
+    tolerance plus what the float32-class operator allows."""
+    import ctypes as C
+    from paper_2509_19747_amd import binding as rb
+    rng = np.random.default_rng(n + nrhs)
+    pts = rng.standard_normal((d, n)).astype(np.float32)
+    kconst, mu, tol = 0.5 / d, 1e-2, 1e-5
+    kop = rr.kernel_operator(rr.OP_RBF, _cuda(pts), kconst, 1.0 / n)
+    P = rr.build_precond(kop, [mu], l=32, sketch="gaussian", seed=7, prec="fp32")
+    B, X0 = rng.standard_normal((n, nrhs)), 0.1 * rng.standard_normal((n, nrhs))
+    Bc = _cuda(B.T)
+    idx = (C.c_int32 * nrhs)(*[0] * nrhs)
+    out = {}
+    for ldx in (n, n + 3):
+        X = torch.full((nrhs, ldx), 7.25, dtype=torch.float64, device="cuda")
+        X[:, :n] = _cuda(X0.T)
+        infos = (rb.rr_solve_info * nrhs)()
+        o = rb.solve_opts(tol=tol, fp64_ir=0)
+        st = rb.lib().rr_solve_batch(P.h, idx, C.c_void_p(Bc.data_ptr()), n, nrhs, C.c_void_p(X.data_ptr()), ldx,
+                                     C.byref(o), infos, C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert st == rr.RR_OK and infos[0].relres_fp64 <= tol + 2e-6 / mu
+        torch.cuda.synchronize()
+        assert bool((X[:, n:] == 7.25).all())
+        out[ldx] = X[:, :n].clone()
+    assert torch.equal(out[n], out[n + 3])
+    op = Operator(kind=rr.OP_RBF, pts=pts, kconst=kconst, scale=1.0 / n)
+    x = out[n + 3].cpu().numpy().T
+    for j in range(nrhs):   # |dA| <= 2e-6 |A|, |A| <= 1, |x| <= |b| / mu
+        assert osol.relres(op.shifted(mu), x[:, j], B[:, j]) <= tol + 2e-6 / mu
