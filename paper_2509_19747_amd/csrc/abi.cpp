@@ -253,6 +253,10 @@ void setup_operator(rr_precond& P, hipStream_t st, int products) {
             launch_sqnorms(A.pts, n, A.d, P.sqn.as<float>(), st);
             P.xa.reset(&P.alloc, (size_t)n * dm * sizeof(float));
             launch_point_records(A.pts, n, A.d, dm, P.xa.as<float>(), st);
+        }
+        // (the float64 products of points past that bound and the blocks of a basis-less
+        // handle read plain records)
+        if (!mma || P.opts.basis == RR_BASIS_LESS) {
             P.xd.reset(&P.alloc, (size_t)n * dm * sizeof(double));
             P.hd.reset(&P.alloc, (size_t)n * sizeof(double));
             launch_point_records64(A.pts, n, A.d, dm, kernel_g64(A.kind, A.kconst), P.xd.as<double>(),
@@ -260,7 +264,7 @@ void setup_operator(rr_precond& P, hipStream_t st, int products) {
         }
         if (mma && products != SETUP_WORK) {
             P.xp.reset(&P.alloc, kernel_mma_record64_bytes(n, dm));
-            if (!P.hd.ptr()) P.hd.reset(&P.alloc, (size_t)n * sizeof(double));
+            if (!P.hd.ptr()) P.hd.reset(&P.alloc, (size_t)n * sizeof(double));   // (the same values)
             launch_kmma_records64(kernel_op_of(P), P.xp.as<double>(), P.hd.as<double>(), st);
         }
         if (P.opts.prec != RR_PREC_FP64 && products != SETUP_F64) {

@@ -1818,3 +1818,41 @@ def test_solve_batch_few_columns_with_longer_columns_of_x(n, d, nrhs):
     x = out[n + 3].cpu().numpy().T
     for j in range(nrhs):   # |dA| <= 2e-6 |A|, |A| <= 1, |x| <= |b| / mu
         assert osol.relres(op.shifted(mu), x[:, j], B[:, j]) <= tol + 2e-6 / mu
+
+
+class _CountingAllocator:
+    """An rr_allocator over torch's that keeps the bytes it has handed out and their peak."""
+
+    def __init__(self):
+        from paper_2509_19747_amd import binding as rb
+        self.sizes, self.live, self.peak = {}, 0, 0
+
+        def alloc(ctx, nbytes, stream):
+            p = torch.cuda.caching_allocator_alloc(int(nbytes), None, stream or 0)
+            self.sizes[p] = int(nbytes)
+            self.live += int(nbytes)
+            self.peak = max(self.peak, self.live)
+            return p
+
+        def free(ctx, ptr, stream):
+            if ptr:
+                self.live -= self.sizes.pop(ptr)
+                torch.cuda.caching_allocator_delete(ptr)
+
+        self._a = rb.rr_allocator._fields_[1][1](alloc)
+        self._f = rb.rr_allocator._fields_[2][1](free)
+        self.struct = rb.rr_allocator(ctx=None, alloc=self._a, free=self._f)
+
+
+@pytest.mark.parametrize("n,d,dm,chunks", [(10_000, 16, 16, 4), (3000, 3, 4, 2), (3000, 20, 32, 7)])
+def test_kernel_handle_holds_each_record_once(n, d, dm, chunks):
+    """A plain handle of a kernel operator: the float32 records and norms, the packed bf16
+    ones (`chunks` pieces of 32 bytes a point, rows and columns) and the packed float64
+    ones with their norms, and nothing else of their size."""
+    al = _CountingAllocator()
+    pts = _cuda(np.random.default_rng(n).standard_normal((d, n)).astype(np.float32))
+    P = rr.build_precond(rr.kernel_operator(rr.OP_RBF, pts, 0.1, 1.0 / n), [1e-3], l=0, prec="fp32", allocator=al)
+    npad = -(-n // 256) * 256
+    assert al.live <= npad * (4 + 4 * dm + 8 + 8 * dm + 2 * 32 * chunks) + 256
+    del P
+    assert al.live == 0
