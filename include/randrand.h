@@ -304,7 +304,10 @@ typedef void (*rr_deliver_fn)(void* user, const rr_request* req, const rr_solve_
                               double t_done);
 
 typedef struct {
-    size_t hbm_budget;    /* device bytes the server may hold for requests               */
+    size_t hbm_budget;    /* device bytes the server may hold for requests; of these, up to
+                             1 GiB of freed blocks stay with the library for the next
+                             call, which counts them against its own budget and gives
+                             them back when a request does not fit beside them          */
     int32_t max_slots;    /* requests resident at once                                  */
     int32_t graph_iters;  /* PCG iterations per replayed batch                          */
     rr_build_opts build;  /* l and seed are taken per request                           */

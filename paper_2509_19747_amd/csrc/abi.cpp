@@ -76,8 +76,10 @@ size_t round_block(size_t bytes) {
     return (bytes + g - 1) / g * g;
 }
 
-void flush_all_caches() {   // caller holds g_cache_mu
+// Caller holds g_cache_mu.  dev >= 0: only the pooled streams of that device.
+void flush_all_caches(int dev = -1) {
     for (auto& c : g_caches) {
+        if (dev >= 0 && (c.dev != dev || !c.pooled)) continue;
         // a stream that is being captured into a graph (by another thread) keeps its
         // blocks: a free queued on it would become part of, or break, that capture
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -157,6 +159,23 @@ void trim_stream_blocks(hipStream_t st, size_t share, size_t bound) {
 void release_cached_blocks() {
     std::lock_guard<std::mutex> lk(g_cache_mu);
     flush_all_caches();
+}
+
+size_t pooled_block_bytes() {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    std::lock_guard<std::mutex> lk(g_cache_mu);
+    size_t b = 0;
+    for (const StreamCache& c : g_caches)
+        if (c.dev == dev && c.pooled) b += c.total;
+    return b;
+}
+
+void release_pooled_blocks() {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    std::lock_guard<std::mutex> lk(g_cache_mu);
+    flush_all_caches(dev);
 }
 
 namespace {

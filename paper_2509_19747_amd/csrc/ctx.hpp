@@ -56,6 +56,9 @@ rr_status guarded(F&& body) {
 void trim_stream_blocks(hipStream_t st, size_t share, size_t bound);
 // Frees every cached block of streams that are not being captured.
 void release_cached_blocks();
+// The same for the pooled streams of this device alone, and the bytes that they hold.
+void release_pooled_blocks();
+size_t pooled_block_bytes();
 
 // Device allocator: the caller's rr_allocator if given, else hipMalloc/hipFree.
 struct Alloc {

@@ -40,15 +40,21 @@ double wall_s() {
     return duration<double>(steady_clock::now().time_since_epoch()).count();
 }
 
-// Device bytes one request holds at its peak (build temporaries included).
-size_t request_bytes(const rr_request& r, bool grouped) {
+// Device bytes one request holds at its peak (build temporaries included) in precision prec.
+size_t request_bytes(const rr_request& r, bool grouped, int32_t prec) {
     const double n = (double)r.n, l = (double)r.l, d = (double)r.d, m = (double)std::max(r.nrhs, 1);
     double b = n * l * (4 + 2 + 8 + 4 + 8 + 16);        // Omega f32/bf16, Q, Y, W, Theta
     b += n * d * 4 + n * 4;                              // points, |x|^2
+    const int dm = rr::kernel_record_len(r.d);
+    b += n * dm * 4 + n * 8 +   // records: float32, float64 norms and packed, packed bf16
+         (double)rr::kernel_mma_record64_bytes(r.n, dm);
+    if (prec != RR_PREC_FP64) b += 2.0 * (double)rr::kernel_mma_record_bytes(r.n, dm);
     b += l * l * 8 * 26 + 4.0 * (2 * l) * (2 * l) * 8;   // l x l factors, GEMM workspace
     const int nr = (int)std::min<double>(m, 8.0);
-    b += 8.0 * (double)std::max(rr::kernel_matvec_ws_doubles(r.n, r.d, nr),   // matvec slot partials
-                                rr::kernel_matvec_ws_doubles(r.n, r.d, 2));
+    const size_t slots = std::max(rr::kernel_matvec_ws_doubles(r.n, r.d, nr),   // matvec slot partials
+                                  rr::kernel_matvec_ws_doubles(r.n, r.d, 2));
+    const bool wide = prec != RR_PREC_FP64 && r.nrhs > rr::KMULTI_MAX;   // packed columns, split partials
+    b += std::max(8.0 * (double)slots, wide ? (double)rr::kernel_matmat_ws_bytes(r.n, r.nrhs) : 0.0);
     b += n * 8 * (8 + 8 * m);                            // CG vectors, batched PCG blocks, B and X
     if (grouped) {
         // slot partials per (padded) column, Q^T R partials and D per column
@@ -60,10 +66,12 @@ size_t request_bytes(const rr_request& r, bool grouped) {
     return (size_t)b;
 }
 
-// Bytes of blocks that the workers of all calls together keep for the next one.  Returning them to the device's
-// pool took 25 ms for a burst of 12 requests served in 32 (0.1 to 0.2 ms a block, one
-// at a time), and the next call's builds as long again to get them.  Like every cached
-// block they go back when an allocation fails.
+// Bytes of blocks that the workers of all calls together keep for the next one (at most the
+// call's budget).  Returning them to the device's pool took 25 ms for a burst of 12
+// requests served in 32 (0.1 to 0.2 ms a block, one at a time), and the next call's builds
+// as long again to get them.  The next call counts them against its budget and gives them
+// back when a request does not fit beside them; like every cached block they also go back
+// when an allocation fails.
 constexpr size_t SERVE_KEEP = (size_t)1 << 30;
 
 struct Job {
@@ -271,10 +279,11 @@ extern "C" rr_status rr_serve(const rr_serve_config* cfg, rr_next_fn next, rr_de
                     run_job(*cfg, job, st, t0, deliver, user, sh);
                 }
                 if (st) {
-                    // the stream goes back to its pool with up to its share of SERVE_KEEP
+                    // the stream goes back to its pool with up to its share of the kept
                     // bytes of cached blocks, for the next call's requests
                     (void)hipStreamSynchronize(st);
-                    trim_stream_blocks(st, SERVE_KEEP / (size_t)cfg->max_slots, SERVE_KEEP);
+                    const size_t keep = std::min(SERVE_KEEP, cfg->hbm_budget);
+                    trim_stream_blocks(st, keep / (size_t)cfg->max_slots, keep);
                     (void)hipStreamSynchronize(st);
                     release_side_stream(side);
                 }
@@ -282,6 +291,7 @@ extern "C" rr_status rr_serve(const rr_serve_config* cfg, rr_next_fn next, rr_de
         }
         std::deque<Job> pending;
         bool ended = false;
+        size_t kept = pooled_block_bytes();   // of earlier calls: held until a request needs the room
         rr_status loop_err = RR_OK;
         while (true) {
             const double now = wall_s() - t0;
@@ -294,7 +304,7 @@ extern "C" rr_status rr_serve(const rr_serve_config* cfg, rr_next_fn next, rr_de
                     const bool valid = r.n >= 1 && r.d >= 1 && r.d <= 32 && r.pts && r.B && r.X &&
                                        r.nrhs >= 1 && r.l >= 0 && r.l <= r.n && std::isfinite(r.mu) &&
                                        r.mu >= 0.0 && (r.kind == RR_OP_RBF || r.kind == RR_OP_MATERN32);
-                    Job j{r, request_bytes(r, cfg->grouped != 0)};
+                    Job j{r, valid ? request_bytes(r, cfg->grouped != 0, cfg->build.prec) : 0};
                     if (!valid || j.bytes > cfg->hbm_budget) {
                         rr_solve_info inf{};
                         inf.status = valid ? RR_ENOMEM : RR_EINVAL;
@@ -313,6 +323,10 @@ extern "C" rr_status rr_serve(const rr_serve_config* cfg, rr_next_fn next, rr_de
                 std::unique_lock<std::mutex> lk(sh.mu);
                 while (!pending.empty() && sh.active < cfg->max_slots &&
                        sh.used + pending.front().bytes <= cfg->hbm_budget) {
+                    if (kept > cfg->hbm_budget - sh.used - pending.front().bytes) {
+                        release_pooled_blocks();
+                        kept = 0;
+                    }
                     Job j = pending.front();
                     pending.pop_front();
                     sh.used += j.bytes;

@@ -1856,3 +1856,59 @@ def test_kernel_handle_holds_each_record_once(n, d, dm, chunks):
     assert al.live <= npad * (4 + 4 * dm + 8 + 8 * dm + 2 * 32 * chunks) + 256
     del P
     assert al.live == 0
+
+
+def _serve_requests(sizes, seed=0):
+    rng = np.random.default_rng(seed)
+    return [dict(kind=rr.OP_RBF, pts=rng.standard_normal((d, n)).astype(np.float32), kconst=0.5 / d, scale=1.0 / max(n, 1),
+                 mu=1e-2, l=l, seed=3, B=rng.standard_normal((n, m)), t_arrival=0.0) for n, d, l, m in sizes]
+
+
+@pytest.mark.parametrize("n,d,l,m,prec", [(1000, 4, 32, 1, "fp32"), (50_000, 32, 64, 1, "fp32"), (100_000, 32, 16, 1, "fp32"),
+                                          (100_000, 32, 0, 64, "fp32"), (3000, 32, 8, 33, "fp32"),
+                                          (60_000, 20, 16, 40, "fp32"), (40_000, 32, 16, 2, "fp64")])
+def test_serving_estimate_covers_what_a_request_holds(n, d, l, m, prec):
+    """The bytes by which a request is admitted are at least the peak of what its buffers and
+    handle take from the allocator (wide records, short sketches, many columns)."""
+    from paper_2509_19747_amd import binding as rb
+    for grouped in (0, 1):
+        al = _CountingAllocator()
+        res, st = rb.serve(_serve_requests([(n, d, l, m)]), max_slots=1, graph_iters=4, grouped=grouped,
+                           build=dict(prec=prec, sketch="gaussian"), solve=dict(tol=1e-2, certify=False, maxit=12),
+                           allocator=al)
+        assert st["served"] == 1 and al.live == 0
+        assert al.peak <= st["hbm_peak"], (grouped, al.peak, st["hbm_peak"])
+
+
+def test_serving_kept_blocks_count_against_the_next_budget():
+    """Blocks that a call keeps for the next one are given back when a request does not fit
+    beside them in its budget, and stay when it does; a call keeps no more than its budget.
+    Requests of no rows are refused."""
+    import ctypes as C
+    from paper_2509_19747_amd import binding as rb
+    pool, used = C.c_void_p(), C.c_uint64()
+
+    def pool_used():   # bytes in use of the device's default pool (attribute 7)
+        torch.cuda.synchronize()
+        assert rb.lib().hipDeviceGetDefaultMemPool(C.byref(pool), 0) == 0
+        assert rb.lib().hipMemPoolGetAttribute(pool, 7, C.byref(used)) == 0
+        return used.value
+
+    kw = dict(graph_iters=8, build=dict(prec="fp32", sketch="gaussian"), solve=dict(tol=1e-6, certify=False))
+    small, big = _serve_requests([(1000, 4, 20, 1)]), _serve_requests([(6000, 8, 180, 2)] * 4)
+    _, st = rb.serve(small, max_slots=1, **kw)
+    budget = st["hbm_peak"] + (1 << 20)
+    _, st = rb.serve(small, hbm_budget=budget, max_slots=1, **kw)
+    assert st["ok"] == 1
+    u0 = pool_used()
+    ref, st = rb.serve(big, max_slots=4, **kw)
+    u1 = pool_used()
+    assert st["ok"] == 4 and u1 - u0 > budget   # (kept, with room in the default budget)
+    _, st = rb.serve(small, max_slots=1, **kw)
+    assert pool_used() - u0 > budget
+    _, st = rb.serve(small, hbm_budget=budget, max_slots=1, **kw)
+    assert st["ok"] == 1 and pool_used() - u0 <= budget
+    again, st = rb.serve(big, max_slots=4, **kw)
+    assert all(np.array_equal(a["X"], b["X"]) for a, b in zip(again, ref))
+    res, st = rb.serve(_serve_requests([(0, 4, 0, 1)]), max_slots=1, **kw)
+    assert st["rejected"] == 1 and res[0]["info"]["status"] == rr.RR_EINVAL
