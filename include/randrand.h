@@ -60,7 +60,10 @@ typedef enum { RR_OP_DENSE = 0, RR_OP_RBF = 1, RR_OP_MATERN32 = 2 } rr_op_kind;
 /*
  * The operator A (not including the shift mu).
  *  DENSE:     A   device, float64, n x n column-major, leading dimension lda >= n,
- *                 symmetric (only its symmetry is assumed, not checked).
+ *                 symmetric (only its symmetry is assumed, not checked).  From a few
+ *                 thousand rows on, the products of rr_solve's iterations and of the tau
+ *                 estimates read the upper triangle alone (A[i + j lda], i <= j); the
+ *                 sketch, the residuals at restarts and every other product read all of A.
  *  RBF:       pts device, float32, structure-of-arrays d x n (pts[k*n + i] is
  *                 coordinate k of point i); A_ij = scale * exp(-kconst ||x_i - x_j||^2).
  *  MATERN32:  same layout; A_ij = scale * (1 + kconst r) exp(-kconst r), r = ||x_i - x_j||.

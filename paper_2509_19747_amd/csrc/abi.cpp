@@ -300,7 +300,7 @@ void setup_operator(rr_precond& P, hipStream_t st, int products) {
 }
 
 int operator_part_count(const rr_precond& P) {
-    return is_kernel(P.op) || P.dense_sym ? kernel_matvec_blocks(P.n) : dense_matvec_blocks(P.n);
+    return is_kernel(P.op) ? kernel_matvec_blocks(P.n) : dense_matvec_blocks(P.n);   // (the triangle's: fewer)
 }
 
 size_t operator_ws_doubles(const rr_precond& P) {
@@ -309,7 +309,7 @@ size_t operator_ws_doubles(const rr_precond& P) {
 }
 
 int apply_operator(const rr_precond& P, const double* u, double mu, double* y, double* dot_part,
-                   double* kmv_ws, bool fp64, const int32_t* stop, hipStream_t st) {
+                   double* kmv_ws, bool fp64, const int32_t* stop, hipStream_t st, bool whole) {
     if (is_kernel(P.op)) {
         const KernelOp k = kernel_op_of(P);
         launch_kernel_matvec(k, fp64 || P.opts.prec == RR_PREC_FP64, u, mu, y, dot_part, kmv_ws,
@@ -319,9 +319,12 @@ int apply_operator(const rr_precond& P, const double* u, double mu, double* y, d
     const bool f32 = !fp64 && P.A32.ptr();
     const void* A = f32 ? P.A32.ptr() : (const void*)P.op.A;
     const int64_t lda = f32 ? P.lda32 : P.op.lda;
-    if (P.dense_sym) launch_dense_matvec_sym(f32 ? DT_F32 : DT_F64, P.n, A, lda, u, mu, y, dot_part, kmv_ws, stop, st);
-    else launch_dense_matvec(f32 ? DT_F32 : DT_F64, P.n, A, lda, u, mu, y, dot_part, stop, st);
-    return operator_part_count(P);
+    if (P.dense_sym && !whole) {
+        launch_dense_matvec_sym(f32 ? DT_F32 : DT_F64, P.n, A, lda, u, mu, y, dot_part, kmv_ws, stop, st);
+        return kernel_matvec_blocks(P.n);
+    }
+    launch_dense_matvec(f32 ? DT_F32 : DT_F64, P.n, A, lda, u, mu, y, dot_part, stop, st);
+    return dense_matvec_blocks(P.n);
 }
 
 void apply_operator_multi(const rr_precond& P, const double* U, int nr, double mu, double* Y,

@@ -180,7 +180,7 @@ struct rr_precond {
     // operator-derived data
     rr::DBuf A32;         // float32 copy of a dense A (FP32 / MIXED), leading dimension lda32
     int64_t lda32 = 0;
-    bool dense_sym = false;   // products read the upper triangle of a stored A only
+    bool dense_sym = false;   // the iterations' products read the upper triangle of a stored A only
     rr::DBuf sqn;         // |x_i|^2 (kernel operators)
     rr::DBuf xa;          // padded point records (kernel operators)
     rr::DBuf rrec, crec;  // packed bf16 records of the MFMA matvec (float32-class handles)
@@ -214,9 +214,12 @@ inline bool is_kernel(const rr_operator& op) { return op.kind == RR_OP_RBF || op
 KernelOp kernel_op_of(const rr_precond& P);
 
 // y = (A + mu I) u with dot partials of u^T y; returns the number of partials.
-// fp64 = use the float64 operator (dense A or float64 kernel entries).
+// fp64 = use the float64 operator (dense A or float64 kernel entries).  whole: a stored A is
+// read whole, also where products read its upper triangle (the true residuals: what a
+// solve reports is the residual of the matrix as given, and an A that is symmetric only to
+// a rounding of its own is refined to that).
 int apply_operator(const rr_precond& P, const double* u, double mu, double* y, double* dot_part,
-                   double* kmv_ws, bool fp64, const int32_t* stop, hipStream_t st);
+                   double* kmv_ws, bool fp64, const int32_t* stop, hipStream_t st, bool whole = false);
 // Same for nr (1 or 2) columns U, Y (n x nr); dot partials of column q start at
 // dot_part + q * operator_part_count(P).
 // Several columns at once; estimate: float32 sums allowed for kernel operators in
@@ -224,7 +227,7 @@ int apply_operator(const rr_precond& P, const double* u, double mu, double* y, d
 void apply_operator_multi(const rr_precond& P, const double* U, int nr, double mu, double* Y,
                           double* dot_part, double* kmv_ws, bool fp64, hipStream_t st,
                           bool estimate = false);
-int operator_part_count(const rr_precond& P);
+int operator_part_count(const rr_precond& P);   // dot partials of any of its products, at most
 // Operator setup (A0): squared norms and point records for kernels, the float32
 // copy of a dense A when the working precision is below float64.  products: the whole
 // handle, or only what the operator products read (both precisions, the working one,

@@ -105,9 +105,9 @@ struct Gen {
     void sync() { RR_HIP(hipStreamSynchronize(st)); }
     const double* Q() const { return P.Qb.as<double>(); }
 
-    // out = A_mu u (fp64: the float64 operator)
-    void opA(const double* u, double* out, const int32_t* stop, bool fp64 = false) {
-        apply_operator(P, u, mu, out, op_part.as<double>(), kws.as<double>(), fp64, stop, st);
+    // out = A_mu u (fp64: the float64 operator; whole: apply_operator)
+    void opA(const double* u, double* out, const int32_t* stop, bool fp64 = false, bool whole = false) {
+        apply_operator(P, u, mu, out, op_part.as<double>(), kws.as<double>(), fp64, stop, st, whole);
     }
     // out = (I - Pi) u with Pi = Q T Q^T
     void comp(const double* u, double* out, const int32_t* stop) {
@@ -305,7 +305,7 @@ rr_status rr_solve_general(const rr_precond* Pc, int32_t mu_index, const double*
             launch_copy_vec(n, b, rc, st);
             rn2 = bb;
         } else {
-            G.opA(x, G.tw.as<double>(), nullptr, ir);
+            G.opA(x, G.tw.as<double>(), nullptr, ir, true);
             launch_residual(n, b, G.tw.as<double>(), rc, G.vpart.as<double>(), st);
             launch_scal_set(G.vpart.as<double>(), vec_blocks(n), G.scal.as<double>() + 1, st);
             RR_HIP(hipMemcpyAsync(&rn2, G.scal.as<double>() + 1, sizeof(double), hipMemcpyDeviceToHost, st));
@@ -390,7 +390,7 @@ rr_status rr_solve_general(const rr_precond* Pc, int32_t mu_index, const double*
     if (ir || P.opts.prec == RR_PREC_FP64) {
         inf.relres_fp64 = relres;
     } else if (o.certify) {
-        G.opA(x, G.tw.as<double>(), nullptr, true);
+        G.opA(x, G.tw.as<double>(), nullptr, true, true);
         launch_residual(n, b, G.tw.as<double>(), rc, G.vpart.as<double>(), st);
         launch_scal_set(G.vpart.as<double>(), vec_blocks(n), G.scal.as<double>() + 1, st);
         double r2 = 0.0;

@@ -96,7 +96,7 @@ struct Solver {
     // r = b - A x (float64 operator if fp64); returns ||r||^2 on the host.
     double true_residual(const double* b, const double* x, bool fp64) {
         apply_operator(P, x, mu, W.w.as<double>(), W.op_part.as<double>(), W.kws.as<double>(), fp64,
-                       nullptr, st);
+                       nullptr, st, true);
         launch_residual(P.n, b, W.w.as<double>(), W.r.as<double>(), W.rr_part.as<double>(), st);
         launch_scal_set(W.rr_part.as<double>(), vec_blocks(P.n), W.scal.as<double>(), st);
         RR_HIP(hipGetLastError());

@@ -1912,3 +1912,24 @@ def test_serving_kept_blocks_count_against_the_next_budget():
     assert all(np.array_equal(a["X"], b["X"]) for a, b in zip(again, ref))
     res, st = rb.serve(_serve_requests([(0, 4, 0, 1)]), max_slots=1, **kw)
     assert st["rejected"] == 1 and res[0]["info"]["status"] == rr.RR_EINVAL
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(krylov="minres"), dict(method="split")])
+@pytest.mark.parametrize("n,prec", [(4097, "fp64"), (5700, "mixed")])
+def test_dense_solve_reports_the_residual_of_the_whole_matrix(n, prec, kw):
+    """A stored matrix that is symmetric only to 1e-8 of its scale (a Gram matrix that was
+    rounded on the way): the solution meets the tolerance with the matrix as given (a tensor
+    of rows, read as the library's columns: A_mu x by its rows), and that residual is
+    the one reported."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    G = torch.randn(n, 40, device="cuda", dtype=torch.float64, generator=g)
+    A = G @ G.T / n
+    A.diagonal().add_(torch.rand(n, device="cuda", dtype=torch.float64, generator=g) * 0.02)
+    A += 1e-8 * A.abs().max() * torch.randn(n, n, device="cuda", dtype=torch.float64, generator=g)
+    mu, tol = 1e-2, 1e-9
+    P = rr.build_precond(rr.dense_operator(A), [mu], l=64, seed=5, prec=prec)
+    b = torch.randn(n, device="cuda", dtype=torch.float64, generator=g)
+    x, info = P.solve(b, tol=tol, **kw)
+    rel = float((b - A @ x - mu * x).norm() / b.norm())
+    # (both sums round: about n eps |A| |x| / |b| <= 4e-12)
+    assert info["relres_fp64"] <= tol and abs(rel - info["relres_fp64"]) <= 4e-12
