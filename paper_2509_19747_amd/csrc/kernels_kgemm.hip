@@ -4,10 +4,11 @@
 // in float64.
 //
 // Both factors (the columns of P scaled by powers of two) are split exactly into three
-// bf16 pieces (24 bits), and the six piece
-// products with combined order <= 2 run on v_mfma_f32_32x32x16_bf16, the smallest
-// first; the three dropped ones are below 2^-26 of the product, a quarter of a float32
-// product's own rounding.  Six bf16 MFMAs take 2.7 times less than the float32 ones
+// bf16 pieces (24 bits), and the six piece products with combined order <= 2 run on
+// v_mfma_f32_32x32x16_bf16, the smallest first.  The three products left off reach 2^-24
+// of the product, a rounding of float32, at worst (2^-27.5 in the mean square over random
+// mantissas, above 2^-26 for 3 % of them), where a float32 MFMA leaves nothing off; the
+// measured errors below include it.  Six bf16 MFMAs take 2.7 times less than the float32 ones
 // they replace (v_mfma_f32_32x32x2_f32 at 142 against 2,270 TFLOP/s).  The entries'
 // exponents come from the packed records of kmma.hpp.
 //

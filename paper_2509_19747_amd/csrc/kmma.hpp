@@ -35,8 +35,6 @@ template <int DM>
 struct KmmaShape {
     static constexpr int KT = 6 * DM + 6;       // record terms
     static constexpr int KB = (KT + 15) / 16;   // MFMA steps
-    static constexpr int BSTR = 16 * KB + 8;    // LDS stride (bf16) of a column record (padded
-                                                // by 16 bytes against bank conflicts)
 };
 
 // Piece of x (row side) and of y (column side) in segment seg.

@@ -1933,3 +1933,35 @@ def test_dense_solve_reports_the_residual_of_the_whole_matrix(n, prec, kw):
     rel = float((b - A @ x - mu * x).norm() / b.norm())
     # (both sums round: about n eps |A| |x| / |b| <= 4e-12)
     assert info["relres_fp64"] <= tol and abs(rel - info["relres_fp64"]) <= 4e-12
+
+
+@pytest.mark.parametrize("n,pad,prec", [(4097, 0, "fp64"), (4352, 1, "fp64"), (7300, 1, "fp64"), (7301, 1, "fp64"),
+                                        (5633, 0, "fp32"), (8192, 0, "fp32"), (10_303, 0, "fp32")])
+def test_triangle_product_through_three_cg_steps(n, pad, prec):
+    """Products that read the upper triangle, in float64 and with the float32 copy, columns on
+    and off 16-byte boundaries, matrices that fit the last-level cache and larger ones:
+    three plain CG steps without refinement, which no restart corrects, against the same
+    steps by torch with the matrix that the handle multiplies by."""
+    from paper_2509_19747_amd import binding as rb
+    g = torch.Generator(device="cuda").manual_seed(n)
+    G = torch.randn(n, 64, device="cuda", dtype=torch.float64, generator=g)
+    A = torch.zeros(n, n + pad, device="cuda", dtype=torch.float64)
+    A[:, :n] = G @ G.T / n
+    A[:, :n].diagonal().add_(torch.rand(n, device="cuda", dtype=torch.float64, generator=g) + 0.1)
+    st = rb.rr_operator(kind=rb.OP_DENSE, n=n, A=A.data_ptr(), lda=n + pad, pts=None, d=0, kconst=0.0, scale=1.0)
+    mu = 1e-2
+    P = rr.build_precond(rb.Operator(st, (A,)), [mu], l=0, prec=prec)
+    b = torch.randn(n, device="cuda", dtype=torch.float64, generator=g)
+    x, info = P.solve(b, tol=1e-15, restart_eta=1e-14, maxit=3, fp64_ir=0, certify=False, ok=(rr.RR_OK, rb.RR_ENOCONV))
+    assert info["iters"] == 3 and info["restarts"] == 0
+    M = A[:, :n] if prec == "fp64" else A[:, :n].float().double()
+    y, r, p = torch.zeros_like(b), b.clone(), b.clone()
+    for _ in range(3):
+        w = M @ p + mu * p
+        rho = r @ r
+        alpha = rho / (p @ w)
+        y, r = y + alpha * p, r - alpha * w
+        p = r + (r @ r) / rho * p
+    # each product's sums round by about n eps |A| |p| <= 2e-12 |p|, and the steps do not
+    # amplify it by more than the condition number (about 20)
+    assert float((x - y).norm() / y.norm()) <= 1e-10
