@@ -19,8 +19,14 @@
 // both tiles are double-buffered in LDS, and a step costs one barrier.  The MFMAs bound
 // it: 12 NT for the product and 3.5 for the entries per wave and step.  n = 20,000,
 // d = 16, 256 columns: 1.26 ms (970 TFLOP/s of bf16 products) where the float32 MFMA
-// kernel took 4.47; n = 5,003, 100 columns: 67 against 500 us.  The relative error
-// against 64 bits is 1.4e-7 to 1.8e-7 over such sizes (1.6e-7 to 2.3e-7 before).
+// kernel took 4.47; n = 5,003, 100 columns: 67 against 500 us.
+//
+// Error against 64 bits, by that of the float32 kernel (two CG steps on 33 to 256 columns,
+// n = 1,000 to 12,000, 2 to 32 coordinates; mean over the columns): RBF 0.6 to 1.0 of it,
+// Matern 0.01 to 0.7, and no more with points 30 from the origin.  A point with itself has
+// distance 0, not what the pieces' rounding leaves of it, and the norms' step comes first,
+// so that the sum of two close points is small when the small pieces are added: without
+// these a Matern product was off by 1.2 to 1.6 times the float32 kernel's error.
 #include "common.hpp"
 #include "ctx.hpp"
 #include "kentry.hpp"
@@ -126,8 +132,13 @@ __global__ __launch_bounds__(KG_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
 #pragma unroll
         for (int e = 0; e < 16; ++e) d[e] = 0.0f;
 #pragma unroll
-        for (int s = 0; s < KB; ++s)
+        for (int e = 0; e < KB; ++e) {
+            const int s = (e + KB - 1) % KB;   // the norms' step first: close points cancel early
             d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cr[kmma_uc<DM, false>(s)], rr_[kmma_uc<DM, true>(s)], d, 0, 0, 0);
+        }
+        if (s0 + i == rtile)   // (uniform) a point with itself
+#pragma unroll
+            for (int e = 0; e < 16; ++e) d[e] = 8 * (e >> 2) + 4 * h + (e & 3) == l32 ? 0.0f : d[e];
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
             bf16x8_t o[3];

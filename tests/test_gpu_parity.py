@@ -1965,3 +1965,20 @@ def test_triangle_product_through_three_cg_steps(n, pad, prec):
     # each product's sums round by about n eps |A| |p| <= 2e-12 |p|, and the steps do not
     # amplify it by more than the condition number (about 20)
     assert float((x - y).norm() / y.norm()) <= 1e-10
+
+
+@pytest.mark.parametrize("kind", [rr.OP_RBF, rr.OP_MATERN32])
+@pytest.mark.parametrize("d", [2, 5, 8, 16, 32])
+def test_wide_product_diagonal(kind, d):
+    """Points so far apart that the matrix is its diagonal: the first CG step of a wide block
+    is B / (scale + mu), up to float32 rounding of the entry, of P and of the product (about
+    2^-24 each) and of their sum; a distance of a point to itself other than 0 shows."""
+    n, m, scale, mu = 700, 40, 0.5, 1e-3
+    rng = np.random.default_rng(d)
+    pts = (1000.0 * rng.standard_normal((d, n))).astype(np.float32)
+    pts[0] = 1000.0 * np.arange(n) + 500.0 * rng.random(n)
+    B = rng.standard_normal((n, m))
+    P = rr.build_precond(rr.kernel_operator(kind, _cuda(pts), 1.0, scale), [mu], l=0, prec="fp32")
+    X, _, _ = P.solve_batch(_cuda(B), [0] * m, tol=1e-15, restart_eta=1e-14, maxit=1, fp64_ir=0, certify=False,
+                            ok=(rr.RR_OK, rr.binding.RR_ENOCONV))
+    assert np.abs(X.cpu().numpy() * (scale + mu) / B - 1.0).max() <= 5e-7
