@@ -20,9 +20,10 @@
 namespace {
 
 // What a call may count against (accepted_bytes), and the array, which also holds what
-// the packed records take beyond that count (at most 10 MiB for any accepted operator).
+// the packed records take beyond that count (at most 6.3 MiB for any accepted operator, with
+// 32 coordinates).
 constexpr size_t kScratchBytes = (size_t)64 << 20;
-constexpr size_t kArrayBytes = (size_t)80 << 20;
+constexpr size_t kArrayBytes = (size_t)72 << 20;
 constexpr int kMaxDevices = 64;
 
 __device__ __align__(256) unsigned char scratch[kArrayBytes];

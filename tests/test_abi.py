@@ -165,3 +165,20 @@ def test_ctypes_structures_match_the_header_layout(tmp_path):
         assert got[(name, "size")] == C.sizeof(s), name
         for f, _ in s._fields_:
             assert got[(name, f)] == getattr(s, f).offset, (name, f)
+
+
+@pytest.mark.parametrize("d,n", [(4, 45220), (8, 44500), (16, 43008), (32, 40232)])
+def test_noalloc_accepts_what_fits_its_count(d, n):
+    """The largest kernel operators that count 64 MiB pass the size check in every precision
+    (they get to the missing device), and one row block more is refused."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("a GPU is present")
+    L = b.lib()
+    buf = np.zeros(16)
+    p = buf.ctypes.data_as(C.c_void_p)
+    for kind in (b.OP_RBF, b.OP_MATERN32):
+        for prec in (b.PREC_FP64, b.PREC_FP32, b.PREC_MIXED):
+            for rows, want in ((n, b.RR_EDEVICE), (n + 256, b.RR_EINVAL)):
+                op = b.rr_operator(kind=kind, n=rows, A=None, lda=0, pts=0x1000, d=d, kconst=1.0, scale=1.0)
+                assert L.rr_apply_operator_noalloc(C.byref(op), 0.0, prec, p, p, None) == want, (prec, rows)
