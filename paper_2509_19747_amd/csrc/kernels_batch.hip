@@ -19,8 +19,8 @@ constexpr int KD_BM = 128, KD_BK = 16, KD_THREADS = 512;
 constexpr int KD_CUS = 256, KD_SPLITS = 16;
 
 // Block: 8 waves in a 2 (rows) x 4 (columns) grid of 64 x 16 NV wave tiles (4 x NV MFMA
-// tiles, 16 NV float64 accumulators per lane), one block a compute unit.  Per step of 16
-// points the block forms the 128 x 16 kernel tile (thread: one row, 4 points whose records
+// tiles, 16 NV float64 accumulators per lane), one block a compute unit by its registers
+// (two of 128 columns with up to four coordinates).  Per step of 16 points the block forms the 128 x 16 kernel tile (thread: one row, 4 points whose records
 // arrive through scalar loads; float64 entries: difference form, float64 exp) into
 // LDS (k-major) and stages the 16 x 64 NV slice of P.
 // The vector ALU does not run beside the float64 MFMA: a step of a wave is about 1100

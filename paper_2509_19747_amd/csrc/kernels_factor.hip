@@ -23,8 +23,8 @@ constexpr int CH_NB = 32;
 // row panel, both row by row: lane j holds column j of A11 and its column of A12 in
 // registers, row k of R11 is read lane by lane into scalars (readlane) and serves the
 // updates of both, all independent of one another, so a step's chain is a square root
-// and a division: 24.7 us a launch (with row k shared through LDS and the solve behind the
-// factorisation, each entry's sum a chain of its own: 30.3).
+// and a division: 24.7 us a launch at l = 1,024, 21.7 at l = 500 (with row k shared through
+// LDS and the solve behind the factorisation, each entry's sum a chain of its own: 30.3).
 // R11 is written back (zeros below the diagonal) where no other block still reads A11: by
 // the only block, or, where several blocks share the row, by one more block of the next
 // launch, which factors prev again.  (Block 0 writing it at once could overtake a block

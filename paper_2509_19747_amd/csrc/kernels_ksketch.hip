@@ -55,7 +55,8 @@ struct Ks2Smem {
 // a load touches 64 contiguous bytes of 16 columns, and its LDS store 128 distinct bytes of
 // banks per eight lanes (with a thread per column, four chunks of it, each load touched 64
 // lines, as long to serve as the step's MFMAs: n = 32,768, 1,024 columns 6.2, so 5.2
-// ms).  B's rows [n, round8(n)) are zero, so a chunk is either inside the padded
+// ms; with 17 to 32 coordinates 29 registers spill, and a build at n = 16,384, l = 512 still
+// goes from 5.76 to 4.79 ms).  B's rows [n, round8(n)) are zero, so a chunk is either inside the padded
 // column or wholly past it; columns past the last are zeros.
 // src: the first column of the wave (wave-uniform: a scalar base and one 32-bit offset keep
 // the addresses out of the registers), cols: the columns from the thread's first one on.

@@ -34,6 +34,10 @@
 // products, the work is a few long blocks per compute unit, and the unit's place is
 // computed, not searched.  n = 50,000, d = 16, one column: 0.40 ms (0.52 before, both
 // under the tracer); two columns at n = 32,768: 0.26 ms (0.45); four: 0.51 (0.66).
+// With 17 to 32 coordinates the variants of four waves a SIMD spill (24 registers for one
+// RBF column, 12 Matern, 11 and 14 for two float columns), and the reloads wait for the
+// copies in flight: little is gained there at large n (a whole product of one column,
+// n = 50,000, d = 32: 0.81 ms, 0.82 with a block a unit; n = 20,000: 0.173, 0.218).
 //
 #include "common.hpp"
 #include "group.hpp"
